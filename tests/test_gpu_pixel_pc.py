@@ -71,6 +71,29 @@ def test_surface_peak_and_shift_random_rolls(fc, H, W):
     compare_pc(prev, cur, sp, pk, rs)
 
 
+@pytest.mark.parametrize("H,W", [(14, 14), (28, 28), (56, 14), (14, 56), (112, 112), (56, 224),
+                                 (224, 28), (448, 896), (896, 896), (896, 14)])
+def test_every_transform_length_both_ways(fc, H, W):
+    """Every length as rows and as columns (one to 32 sequences in a wave, the last strip of
+    columns 1, 5, 7 or 8 wide), more items than one; the shift and peak are the same bytes
+    whether or not the surface is asked for."""
+    rng = np.random.default_rng(H * 1009 + W)
+    B = 2
+    prev = rng.random((B, 3, H, W)).astype(np.float32)
+    cur = np.stack([np.roll(prev[b], (H // 5 + b, -(W // 4)), axis=(1, 2)) for b in range(B)])
+    cur = np.clip(cur + rng.normal(0, 0.02, cur.shape), 0, 1).astype(np.float32)
+    ctx = ctx_for(fc, B, H, W)
+    try:
+        sp, pk, rs = run_pc(fc, ctx, prev, cur)
+        sp2 = torch.empty(B, 2, dtype=torch.float64, device="cuda")
+        fc.fc_phase_correlate(ctx, torch.from_numpy(prev).cuda(), torch.from_numpy(cur).cuda(), sp2)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    compare_pc(prev, cur, sp, pk, rs)
+    np.testing.assert_array_equal(sp, sp2.cpu().numpy())
+
+
 def test_trajectory_pairs_and_missing_previous(fc):
     """Consecutive 448 x 448 frames of the benchmark trajectory, and batches without a
     previous frame or with an all-black one (shift 0, zero surface, as in the oracle)."""
