@@ -263,7 +263,7 @@ fc_status fc_create(fc_ctx **out, int32_t device, const fc_caps *caps) {
       (st = dev_alloc(&ctx->rope, (size_t)c.max_seq * 64, "rope")) != FC_OK ||
       (st = dev_alloc(&ctx->stage, ctx->stage_elems, "stage")) != FC_OK ||
       (ctx->krot_elems && (st = dev_alloc(&ctx->krot, ctx->krot_elems, "rotated keys")) != FC_OK) ||
-      (st = dev_alloc(&ctx->vit_rows, B + 1, "vision rows")) != FC_OK ||
+      (st = dev_alloc(&ctx->vit_rows, B, "vision rows")) != FC_OK ||
       (st = dev_alloc(&ctx->vit_rope, (size_t)128 * 32, "vision rotary table")) != FC_OK ||
       (st = fc::upload_select_tables()) != FC_OK) {
     free_ws(ctx);
@@ -627,7 +627,7 @@ static fc_status check_vit(fc_ctx *ctx, const fc_vit_desc *L, const fc_vit_cache
   const long slots = (long)B * N * c->merge * c->merge;
   const fc_caps &cp = ctx->caps;
   const long rows = (long)cp.max_batch * cp.max_tokens;
-  // the O reduction's sums of squares: one per slot and 1024-column chunk
+  // the row sums of squares of the layer: one per slot and 1024-column chunk
   const long ssq_cap = rows * std::max<long>(8, (cp.max_d_model + 127) / 128);
   if (B > cp.max_batch || N > cp.max_tokens || slots * L->d_model > rows * cp.max_d_model ||
       slots * L->d_model > rows * cp.max_qkv || slots * L->d_ffn > rows * cp.max_ffn ||

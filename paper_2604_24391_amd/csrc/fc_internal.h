@@ -47,7 +47,6 @@ constexpr int kMaxSplits = 16;
 // Layer calls with at least this many token slots (B * N) run the large-M path:
 // square MFMA tiles with fused epilogues and keys rotated once per call.
 constexpr long kBigRows = 2048;
-constexpr long kPlainBigRows = 512;  // rows from which run_plain_gemm takes the 256 x 256 tiles
 
 // ----------------------------------------------------------------------------- context
 struct ProfRec {
@@ -84,8 +83,7 @@ struct fc_ctx {
   size_t krot_elems = 0;
   unsigned char *pix = nullptr;  // pixel phase-correlation workspace, allocated at first use
   size_t pix_bytes = 0;
-  int32_t *vit_rows = nullptr;  // [max_batch + 1] recomputed patch rows per item (vision
-                                // block), then the split count of the last many-row GEMM
+  int32_t *vit_rows = nullptr;  // [max_batch] recomputed patch rows per item (vision block)
   float2 *vit_rope = nullptr;   // [128][32] vision rotary (cos, sin) by position, frequency
   uint16_t *vlog = nullptr;     // [B][S][kv row] values in row order (slot-mapped caches,
   size_t vlog_elems = 0;        // many-row layer calls only), allocated at first use
@@ -202,17 +200,11 @@ __device__ __forceinline__ int pool_row(const int32_t *map, int b, int S, int r)
 }
 
 // Split-K partial sums of A[B N][K] W[Nout][K]^T over the first nrec[b] rows of each
-// item, no epilogue; K a multiple of 64, Nout of 16.  Few rows: the weight-streaming GEMM,
-// part = C[split][B N][Nout], *splits = its split count, *dsplits_used = null, *tiles = 0.
-// Many rows (and dsplits given): the 256 x 256-tile GEMM over the rows packed across
-// items (item b's rows after those of items < b), part = [split][V][ceil(Nout / 256)]
-// tiles of [256 packed rows][256 columns], V = ceil(packed rows / 256); its split count
-// (at most 8) is decided on the device and written to *dsplits; *splits = 8,
-// *dsplits_used = dsplits and *tiles = 1.
+// item, no epilogue; K a multiple of 64, Nout of 16: the weight-streaming GEMM,
+// part = C[split][B N][Nout], *splits = its split count.
 fc_status run_plain_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const uint16_t *A,
                          const uint16_t *W, int K, int Nout, int N, const int32_t *nrec,
-                         float *part, int B, int *splits, int *dsplits,
-                         const int **dsplits_used, int *tiles);
+                         float *part, int B, int *splits);
 
 // Vision-encoder block with partial recompute and its cache update (vit.hip).
 // Reused tokens' K/V rows (and output rows, when y_prev is given) copied from a previous

@@ -30,35 +30,14 @@
 #include <cstdint>
 
 #include "fc_internal.h"
+#include "gemm_dev.h"
 
 namespace fc {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ float bf2f(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  // round to nearest even (inputs are finite)
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 struct alignas(16) U16x8 {
   uint16_t v[8];
 };
-
-// Device-side counts and ids come from fc_select; clamp them so that a caller
-// passing anything else can never make a kernel leave its buffers.
-// Null counts and ids (the trailing-text rows) mean every token of the region, in order.
-__device__ __forceinline__ int n_valid(const int32_t *nrec, int b, int N) {
-  return nrec ? min(max(nrec[b], 0), N) : N;
-}
-__device__ __forceinline__ int tok_of(const int32_t *idx, long slot, int N) {
-  return idx ? min(max(idx[slot], 0), N - 1) : (int)(slot % N);
-}
 
 // RoPE position of rotary frequency pair k for the token at sequence position seqpos
 // (its index in the current step's prompt, which also decides causality).  1-D RoPE:
@@ -107,9 +86,7 @@ __device__ __forceinline__ int rope_pos(const MRope &m, int seqpos, int k) {
 // Split-K partial sums go to a float32 buffer [split][rows][cols] that the k_red_*
 // kernels reduce; the SwiGLU mode applies the MLP RMSNorm and SiLU(g) * u in its own
 // epilogue.
-enum { G_QKV = 0, G_O = 1, G_GU = 2, G_DOWN = 3, G_PLAIN = 4 };   // PLAIN: fp32 sums only (k_mgemm)
-constexpr int KS = kGemmBK;                 // 64 K values per step
-constexpr int RB = KS * 2;                  // bytes per staged operand row
+enum { G_QKV = 0, G_O = 1, G_GU = 2, G_DOWN = 3 };
 constexpr int MT = 256;                     // rows per M tile
 constexpr int kLdsBytes = 158 * 1024;       // operand stages
 constexpr int kGainSteps = 2 * MT * 4 / (KS * 2);   // K steps of gain the QKV LDS slice holds
@@ -130,74 +107,6 @@ struct WArgs {
   int ss_parts;
   float eps;
 };
-
-// Workgroup id -> tile id so that each XCD (workgroups are dealt round-robin over
-// the 8 XCDs) works on a contiguous range of tiles.
-__device__ __forceinline__ int xcd_tile(int w, int total) {
-  const int per = total / 8;
-  if (w >= per * 8) return w;
-  return (w & 7) * per + (w >> 3);
-}
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-// LDS DMA of 16 B per lane to lds + 16 * lane (lds must be wave-uniform).  M0 is
-// reserved to the compiler, so the asm restores it.
-__device__ __forceinline__ void dma16(const void *gp, uint32_t lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(gp), "s"(l)
-      : "memory");
-}
-// The same for data read once (streamed weights): the non-temporal hint keeps such
-// lines from displacing the re-read activation rows in L2.
-__device__ __forceinline__ void dma16_nt(const void *gp, uint32_t lds) {
-  const uint32_t l = __builtin_amdgcn_readfirstlane(lds);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %1, off nt\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(gp), "s"(l)
-      : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt holds at most 63 outstanding loads");
-  __builtin_amdgcn_s_waitcnt(0x3F70 | (N & 0xF) | ((N >> 4) << 14));
-}
-// wait until at most n (wave-uniform, < 64) of this wave's loads are outstanding
-__device__ __forceinline__ void wait_vm_rt(int n) {
-  switch (n) {
-#define FC_W1(x) case x: wait_vm<x>(); break;
-#define FC_W8(x) FC_W1(x) FC_W1(x + 1) FC_W1(x + 2) FC_W1(x + 3) FC_W1(x + 4) FC_W1(x + 5) FC_W1(x + 6) FC_W1(x + 7)
-    FC_W8(0) FC_W8(8) FC_W8(16) FC_W8(24) FC_W8(32) FC_W8(40) FC_W8(48) FC_W8(56)
-#undef FC_W8
-#undef FC_W1
-    default: wait_vm<0>(); break;
-  }
-}
-// Workgroup barrier that orders LDS accesses only: global loads in flight stay in
-// flight across it (the full fence of __syncthreads would drain them).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-__device__ __forceinline__ int swz8(int row) { return (row >> 1) & 7; }
 
 template <int MODE>
 struct WTraits {
@@ -701,7 +610,6 @@ constexpr int MB = 256;                     // tile rows and staged weight rows
 constexpr int kMStage = 2 * MB * RB;        // 64 KB per stage
 constexpr int kMSsqCols = 256;              // columns per sum-of-squares partial
 constexpr int kMEpPitch = MB + 4;           // floats per row of the epilogue tile
-constexpr int kMMaxItems = 1024;            // batch items the packed row map holds
 
 struct MArgs {
   const uint16_t *A;              // bf16 activations, one row per slot
@@ -713,25 +621,8 @@ struct MArgs {
   int cus;                        // workgroup slots: one resident workgroup per CU
   int part_units;                 // 256 x 256 fp32 tiles the partial buffer holds
   float *part;                    // K-range partial tiles of the split tail
-  float *out;                     // G_PLAIN output: [ks][V][ntn] tiles of 256 x 256 fp32
-  int *ks_out;                    // G_PLAIN: the K-range part count ks, written by workgroup 0
   RedArgs r;                      // epilogue operands (as the reductions use them)
 };
-
-// G_PLAIN: when the tiles fill at most half the CUs, every tile runs as ks K-range parts
-// (at most kPlainMaxParts, at least 4 K steps each), written as separate sums that the
-// consumer adds.
-constexpr int kPlainMaxParts = 8;
-__host__ __device__ inline int plain_split(int tiles, int cus, int nk) {
-  int ks = 1;
-  if (tiles > 0 && 2 * tiles <= cus) {
-    ks = cus / tiles;
-    ks = ks < kPlainMaxParts ? ks : kPlainMaxParts;
-    ks = ks < nk / 4 ? ks : nk / 4;
-    ks = ks > 1 ? ks : 1;
-  }
-  return ks;
-}
 
 // With one workgroup per CU, tiles run in rounds of `cus`.  When there are few rounds
 // and the last is at most half full, its `tail` tiles run as `ks` parts over K ranges
@@ -770,48 +661,6 @@ __device__ __forceinline__ void mtile_of(int V, int ntn, int bid, int &mt, int &
   mt = base + (li - nt * gsz);
 }
 
-__device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d) {
-  return make_uint2(f2bf(a) | ((uint32_t)f2bf(b) << 16), f2bf(c) | ((uint32_t)f2bf(d) << 16));
-}
-__device__ __forceinline__ float4 unpack_bf16x4(uint2 u) {
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-}
-
-// The gathered rows of all items, packed: packed row p is slot b * N + (p - pre[b]) of
-// the item b with pre[b] <= p < pre[b + 1] (pre = exclusive prefix sums of the
-// recompute counts), so only the last tile of the whole batch is partly empty.
-__device__ __forceinline__ long packed_slot(const int *pre, int B, int N, int p, int &b) {
-  int lo = 0, hi = B - 1;                       // largest b with pre[b] <= p
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (pre[mid] <= p) lo = mid; else hi = mid - 1;
-  }
-  b = lo;
-  return (long)lo * N + (p - pre[lo]);
-}
-
-// Exclusive prefix sums of the recompute counts into pre[0..B] (wave 0; the caller
-// synchronises): each lane sums a run of items, then the runs are scanned.
-__device__ __forceinline__ void mg_prefix(const MArgs &a, int *pre) {
-  const int lane = threadIdx.x & 63;
-  const int per = (a.B + 63) / 64, i0 = lane * per;
-  int run = 0;
-  for (int i = i0; i < min(i0 + per, a.B); ++i) run += n_valid(a.r.nrec, i, a.N);
-  int inc = run;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(inc, o);
-    if (lane >= o) inc += v;
-  }
-  int acc_run = inc - run;
-  for (int i = i0; i < min(i0 + per, a.B); ++i) {
-    pre[i] = acc_run;
-    acc_run += n_valid(a.r.nrec, i, a.N);
-  }
-  if (lane == 63) pre[a.B] = inc;
-}
-
 // Epilogue of 8 tile rows, rows(it) for it = 0..7, by one wave: trow(it) holds the row's
 // 256 accumulated columns (SwiGLU: the 128 products), lane l handles columns
 // 4 l .. 4 l + 3.  The rows' slots, token ids and residual inputs are loaded for all 8
@@ -833,7 +682,7 @@ __device__ __forceinline__ void mg_epi_rows8(const MArgs &a, const int *pre, Row
     rv[it] = rows(it) < nvalid;
     bi[it] = 0;
     slot[it] = rv[it] ? packed_slot(pre, a.B, a.N, row0 + rows(it), bi[it]) : 0;
-    tok[it] = (MODE != G_GU && MODE != G_PLAIN && rv[it]) ? tok_of(r.idx, slot[it], a.N) : 0;
+    tok[it] = (MODE != G_GU && rv[it]) ? tok_of(r.idx, slot[it], a.N) : 0;
   }
   // residual inputs: x rows for O, h1 rows for down
   uint2 xin[MODE == G_O ? 8 : 1];
@@ -928,38 +777,25 @@ __global__ __launch_bounds__(512) void k_mgemm(MArgs a) {
   __shared__ int pre[kMMaxItems + 1];
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  if (w == 0) mg_prefix(a, pre);
+  if (w == 0) row_prefix(a.r.nrec, a.B, a.N, pre);
   __syncthreads();
   // the grid covers every slot; only the tiles of the packed rows run, the tail
   // tiles as K-range parts
   const int V = (pre[a.B] + MB - 1) / MB;
   const int nk = a.K / KS;
   const int bid = blockIdx.x;
-  int split = 0;
   int mt, nt, kb = 0, ke = nk, unit = -1;
-  if (MODE == G_PLAIN) {
-    // every tile as ks K-range parts, part p of tile i at workgroup p V ntn + i
-    const int T = V * a.ntn;
-    const int ks = plain_split(T, a.cus, nk);
-    if (bid == 0 && t == 0) *a.ks_out = ks;
-    if (bid >= T * ks) return;
-    split = bid / T;
-    mtile_of(V, a.ntn, bid - split * T, mt, nt);
-    kb = split * nk / ks;
-    ke = (split + 1) * nk / ks;
+  int F, tail, ks;
+  mtail_split(V * a.ntn, a.cus, a.part_units, nk, F, tail, ks);
+  if (bid >= F + tail * ks) return;
+  if (bid < F) {
+    mtile_of(V, a.ntn, bid, mt, nt);
   } else {
-    int F, tail, ks;
-    mtail_split(V * a.ntn, a.cus, a.part_units, nk, F, tail, ks);
-    if (bid >= F + tail * ks) return;
-    if (bid < F) {
-      mtile_of(V, a.ntn, bid, mt, nt);
-    } else {
-      const int u = bid - F, ti = u % tail, kp = u / tail;
-      mtile_of(V, a.ntn, F + ti, mt, nt);
-      kb = kp * nk / ks;
-      ke = (kp + 1) * nk / ks;
-      unit = ti * ks + kp;
-    }
+    const int u = bid - F, ti = u % tail, kp = u / tail;
+    mtile_of(V, a.ntn, F + ti, mt, nt);
+    kb = kp * nk / ks;
+    ke = (kp + 1) * nk / ks;
+    unit = ti * ks + kp;
   }
   const int row0 = mt * MB;
   const int nvalid = min(MB, pre[a.B] - row0);
@@ -1051,23 +887,6 @@ __global__ __launch_bounds__(512) void k_mgemm(MArgs a) {
   }
   lds_barrier();                                               // the stages are free
 
-  if (MODE == G_PLAIN) {
-    // the raw K-range sums straight from the accumulators, tile-contiguous: part `split`
-    // of tile (mt, nt) is the [256 packed rows][256 columns] block at
-    // ((split V + mt) ntn + nt) 256^2, V the valid M tiles (rows past the packed rows are
-    // not stored)
-    float *ob = a.out + (((long)split * V + mt) * a.ntn + nt) * (MB * MB);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int rr = wm * 128 + i * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
-        if (rr >= nvalid) continue;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) ob[rr * MB + wn * 64 + j * 32 + l32] = acc[i][j][e];
-      }
-    return;
-  }
   if (unit >= 0) {
     // a part of a tail tile: the raw fp32 accumulators, [256 rows][256 staged columns]
     float *pt = a.part + (long)unit * (MB * MB);
@@ -1125,7 +944,7 @@ __global__ __launch_bounds__(512) void k_mtail(MArgs a) {
   __shared__ int pre[kMMaxItems + 1];
   const int t = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  if (w == 0) mg_prefix(a, pre);
+  if (w == 0) row_prefix(a.r.nrec, a.B, a.N, pre);
   __syncthreads();
   const int V = (pre[a.B] + MB - 1) / MB;
   const int nk = a.K / KS;
@@ -2251,40 +2070,7 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
 
 fc_status run_plain_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const uint16_t *A,
                          const uint16_t *W, int K, int Nout, int N, const int32_t *nrec,
-                         float *part, int B, int *splits, int *dsplits, const int **dsplits_used,
-                         int *tiles) {
-  *dsplits_used = nullptr;
-  // many rows: the 256 x 256-tile GEMM, each tile as up to 8 K-range parts whose sums go
-  // to part as 256 x 256 tiles over the packed rows; the part count is decided on the
-  // device (it depends on the row counts there) and written to *dsplits for the consumer
-  const long mtiles = ((long)B * N + MB - 1) / MB, ntn = (Nout + MB - 1) / MB;
-  const int cus = std::max(ctx->num_cus, 1);
-  // the most tiles any row count can store: V ntn ks(V) over V <= mtiles
-  long most = 0;
-  for (long V = 1; V <= mtiles && V * ntn <= INT32_MAX; ++V)
-    most = std::max(most, V * ntn * plain_split((int)(V * ntn), cus, K / KS));
-  *tiles = 0;
-  if (dsplits && (long)B * N >= kPlainBigRows && B <= kMMaxItems && K % KS == 0 &&
-      Nout % 16 == 0 && most > 0 && (size_t)most * MB * MB <= ctx->part_elems) {
-    MArgs m{};
-    m.A = A; m.W0 = W;
-    m.K = K; m.Nout = Nout; m.N = N; m.B = B;
-    m.r.nrec = nrec;
-    m.out = part;
-    m.ks_out = dsplits;
-    m.mtiles = (int)(((long)B * N + MB - 1) / MB);
-    m.ntn = (Nout + MB - 1) / MB;
-    m.cus = cus;
-    const long total = (long)m.mtiles * m.ntn * kPlainMaxParts;
-    if (total > INT32_MAX) return fail(FC_ERR_CAPACITY, "%s: too many tiles", name);
-    ProfScope ps(ctx, st, name);
-    hipLaunchKernelGGL(k_mgemm<G_PLAIN>, dim3((unsigned)total), dim3(512), 0, st, m);
-    FC_LAUNCH_OK(st, "k_mgemm");
-    *splits = kPlainMaxParts;
-    *dsplits_used = dsplits;
-    *tiles = 1;
-    return FC_OK;
-  }
+                         float *part, int B, int *splits) {
   WArgs g{};
   g.A = A; g.W0 = W;
   g.K = K; g.Nout = Nout; g.N = N; g.nrec = nrec;

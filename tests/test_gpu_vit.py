@@ -400,3 +400,25 @@ def test_block_variants(fc, ctx, d, heads, hd, ffn, gh, gw, m, window, B):
     pct = [60, 15, 100][:B]
     ids = [np.sort(fcdata.random_reuse_ids(401 + b, n, p)) for b, p in enumerate(pct)]
     c.check(fc, ctx, ids)
+
+
+@pytest.mark.parametrize("shape,gh,gw,m,window,counts", [
+    ("qwen", 16, 16, 2, 0, [256]),          # 1024 rows: the tallest tiles; 16 key blocks of a frame
+    ("qwen", 16, 16, 2, 4, [161]),          # 644 rows, a partial last tile of 4 rows
+    ("qwen", 9, 7, 2, 4, [1, 63, 0]),       # 4 to 252 rows in ragged windows, an empty item
+    ("qwen", 8, 8, 2, 4, [8]),              # 32 rows: one tile of the lowest kind
+    ("hd16", 5, 9, 2, 2, [45, 17]),         # head dim 16, one K step, windows of 16 keys
+    ("hd48", 7, 5, 2, 0, [35, 34]),         # head dim 48 (12 pairs to a quarter), 140 keys
+    ("hd112", 6, 6, 2, 5, [36, 9, 20]),     # head dim 112, windows of 100, 20 and 4 keys
+])
+def test_gemm_tiles_and_key_blocks(fc, ctx, shape, gh, gw, m, window, counts):
+    """Row counts at which the projections take another tile (32 to 128 rows high, 64 to 256
+    staged columns), tiles cut by the last row and by the last columns, items packed into one
+    tile, and the attention's key blocks cut by the window."""
+    sh = {"qwen": fcdata.QWEN_VIT, "hd16": fcdata.VitShape(d=64, heads=4, hd=16, ffn=64),
+          "hd48": fcdata.VitShape(d=192, heads=4, hd=48, ffn=320),
+          "hd112": fcdata.VitShape(d=448, heads=4, hd=112, ffn=192)}[shape]
+    c = VitCase(sh, gh, gw, m, window, len(counts), seed=700 + gh * gw + window)
+    rng = np.random.default_rng(701)
+    ids = [np.sort(rng.permutation(gh * gw)[:n]).astype(np.int32) for n in counts]
+    c.check(fc, ctx, ids)
