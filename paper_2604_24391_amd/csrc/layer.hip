@@ -4,23 +4,24 @@
 // token of batch item b, j < n_recompute[b] (read on the device, so no host
 // sync); grids are sized for N rows per item and surplus tiles exit.
 //
+//   k_gather_norm  the recomputed tokens' rows of x by id, RMS-normalised, as the QKV
+//               GEMM's bf16 operand.
+//   k_row_gemm  QKV (bias, rotated q stored, raw k and v scattered into the current frame's
+//               cache rows), O (residual -> h1 in float32, the SwiGLU operand
+//               bf16(h1 * g_mlp) and sums of squares of h1) and short down projections
+//               (residual, output rows scattered): row tiles over the slots, whole K range.
 //   k_wgemm     weight-streaming bf16 MFMA GEMM (v_mfma_f32_16x16x32_bf16) over the
-//               slots, C = A W^T with W row-major [out][in] like torch.nn.Linear;
-//               split-K float32 partials, or (SwiGLU) SiLU(g) * u in the epilogue.
-//               The QKV projection gathers the recomputed tokens' rows of x by id and
-//               multiplies x g (the attention RMSNorm gain) on its A fragments.
-//   k_red_qkv   sums the QKV partials, scales by the token's 1/rms, adds the bias,
-//               stores rotated q and scatters raw k and v into the current frame's
-//               cache rows.
+//               slots, C = A W^T with W row-major [out][in] like torch.nn.Linear:
+//               SiLU(g) * u in the epilogue (SwiGLU), or split-K float32 partials (long
+//               down projections).
+//   k_mgemm     all four projections with thousands of rows.
 //   k_attn      attention of the gathered queries over the whole cache, GQA
 //               (one wave per query head of a KV group), RoPE applied to q and to
 //               each key block as it is staged in LDS, causal by position, float32
 //               online softmax in the transposed form S^T = K Q^T so that a lane
 //               owns one query column.  Optional split over key blocks.
 //   k_attn_combine  merges split-KV partials.
-//   k_red_o     residual add -> h1 (float32), the SwiGLU operand bf16(h1 * g_mlp)
-//               and per-chunk sums of squares of h1 for the MLP RMSNorm.
-//   k_red_down  residual add, bf16 output rows scattered into the output cache.
+//   k_red_down  sums k_wgemm's partials: residual add, bf16 output rows scattered into the output cache.
 //   k_cache_update  copies cached K/V/output rows of each reused token from its
 //               aligned source token.
 #include <hip/hip_runtime.h>
@@ -31,6 +32,7 @@
 
 #include "fc_internal.h"
 #include "gemm_dev.h"
+#include "rowgemm.h"
 
 namespace fc {
 namespace {
@@ -39,28 +41,6 @@ struct alignas(16) U16x8 {
   uint16_t v[8];
 };
 
-// RoPE position of rotary frequency pair k for the token at sequence position seqpos
-// (its index in the current step's prompt, which also decides causality).  1-D RoPE:
-// seqpos itself.  Multimodal RoPE (Qwen2.5-VL): pairs [0, s1) rotate by the temporal,
-// [s1, s2) by the row and [s2, hd/2) by the column position; a text token has all three
-// equal to its index, the token (I, J) of the frame with logical index l has
-// (st, st + I, st + J) with st = T + l span, span = max(grid rows, grid columns), each
-// frame taking span positions after the one before it.
-// Text after the frames continues from the last frame's span: its three positions are
-// T + W span + (its index past the frames).
-struct MRope {
-  int on, T, N, W, gw, span, s1, s2;
-};
-__device__ __forceinline__ int rope_pos(const MRope &m, int seqpos, int k) {
-  if (!m.on || seqpos < m.T) return seqpos;
-  if (seqpos >= m.T + m.W * m.N) return seqpos - m.W * m.N + m.W * m.span;
-  const int r = seqpos - m.T, l = r / m.N, tok = r - l * m.N;
-  const int st = m.T + l * m.span;
-  if (k < m.s1) return st;
-  const int I = tok / m.gw;
-  return k < m.s2 ? st + I : st + (tok - I * m.gw);
-}
-
 // ------------------------------------------------------------------------------- GEMM
 // Weight-streaming GEMM over the gathered rows, C[rows][cols] = A[rows][K] W[cols][K]^T
 // with W row-major [out][in] like torch.nn.Linear.  With a few hundred gathered rows
@@ -68,9 +48,9 @@ __device__ __forceinline__ int rope_pos(const MRope &m, int seqpos, int k) {
 // whole activation tile for its columns, so the kernel is shaped by the per-CU load
 // path:
 //   * output columns are dealt in 16-column blocks evenly over all CUs (SwiGLU: the gate
-//     block and the up block of the same columns form a pair); the QKV, O and down
-//     projections add a K split so that the column groups times the splits cover the
-//     chip once, each split's activation K-slice staying in one XCD's L2;
+//     block and the up block of the same columns form a pair); a projection without a pair
+//     adds a K split so that the column groups times the splits cover the chip once, each
+//     split's activation K-slice staying in one XCD's L2;
 //   * a K step stages 64 K values of every operand row -- one full 128-B line per row,
 //     8 rows per 1 KB DMA instruction (half lines double the request count) -- into LDS
 //     by global_load_lds.  Rows are unpadded, their 16-B chunks XOR-swizzled by
@@ -83,23 +63,21 @@ __device__ __forceinline__ int rope_pos(const MRope &m, int seqpos, int k) {
 //     into accumulators that are never stored;
 //   * PD stages rotate with one LDS barrier per K step: after barrier k the loaders
 //     refill the stage of step k - 1 with step k + PD - 1.
-// Split-K partial sums go to a float32 buffer [split][rows][cols] that the k_red_*
-// kernels reduce; the SwiGLU mode applies the MLP RMSNorm and SiLU(g) * u in its own
-// epilogue.
+// Split-K partial sums go to a float32 buffer [split][rows][cols] that k_red_down (or the
+// merger's reductions) adds up; the SwiGLU mode applies the MLP RMSNorm and SiLU(g) * u in
+// its own epilogue.  The decoder's QKV and O projections and short down projections with few
+// rows take the row tiles of rowgemm.h instead; the 256 x 256 tiles below use all four modes.
 enum { G_QKV = 0, G_O = 1, G_GU = 2, G_DOWN = 3 };
 constexpr int MT = 256;                     // rows per M tile
 constexpr int kLdsBytes = 158 * 1024;       // operand stages
-constexpr int kGainSteps = 2 * MT * 4 / (KS * 2);   // K steps of gain the QKV LDS slice holds
 
 struct WArgs {
-  const uint16_t *A;              // bf16 activations: one row per slot, or (gather) x [B][N][K]
-  int gather;                     // QKV: A rows are the layer input's rows at the token ids
-  const uint16_t *gain;           // QKV: attention RMSNorm gain, applied along K to A
+  const uint16_t *A;              // bf16 activations: one row per slot
   const uint16_t *W0, *W1;        // weights [cols][K]; SwiGLU: gate, up
   int K, Nout, N;                 // N = token slots per batch item
   int nb, ncg, splits, ksteps;    // 16-col blocks, column groups, K splits, K steps per split
   int tpb;                        // M tiles per batch item
-  const int32_t *idx, *nrec;
+  const int32_t *nrec;
   float *part;                    // [split][B*N][Nout]
   long rows;                      // B*N
   uint16_t *act;                  // SwiGLU output [B*N][Nout]
@@ -111,9 +89,8 @@ struct WArgs {
 template <int MODE>
 struct WTraits {
   // 16-column blocks a column group may hold: 1184 SwiGLU pairs over 256 groups is
-  // 4.625; the Qwen QKV (288 blocks) and O/down (224 blocks) split into 32 groups of 9
-  // and 7
-  static constexpr int NBLK = MODE == G_GU ? 5 : (MODE == G_QKV ? 9 : 7);
+  // 4.625; the Qwen down projection (224 blocks) splits into 32 groups of 7
+  static constexpr int NBLK = MODE == G_GU ? 5 : 7;
   static constexpr int NBW = (MODE == G_GU ? 2 : 1) * NBLK;   // staged weight blocks
 };
 template <int MODE, int MBW>
@@ -126,6 +103,21 @@ struct WStage {
   static_assert(PD >= 3, "at least three stages");
   static_assert((PD - 2) * MAXI < 64, "vmcnt holds at most 63 outstanding loads");
 };
+
+// Sum of a row's n partial sums of squares, four at a time where the row is aligned to that.
+__device__ __forceinline__ float sum_row(const float *p, int n) {
+  float v = 0.f;
+  if (n % 4 == 0) {
+#pragma unroll 4
+    for (int c = 0; c < n; c += 4) {
+      const f32x4 u = *reinterpret_cast<const f32x4 *>(p + c);
+      v += (u[0] + u[1]) + (u[2] + u[3]);
+    }
+  } else {
+    for (int c = 0; c < n; ++c) v += p[c];
+  }
+  return v;
+}
 
 // One (M tile, column group, K split) with MBW 16-row blocks per MFMA wave.
 template <int MODE, int MBW>
@@ -163,8 +155,7 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
       if (j < nA) {
         const int r = j * 8 + rsub;                            // tile row
         const int rr = r < nvalid ? r : nvalid - 1;            // clamp: never stored
-        const long arow = a.gather ? (long)b * a.N + tok_of(a.idx, slot0 + rr, a.N) : slot0 + rr;
-        gp[i] = a.A + arow * a.K + k0 + ((ch ^ swz8(r)) * 8);
+        gp[i] = a.A + (slot0 + rr) * a.K + k0 + ((ch ^ swz8(r)) * 8);
         lo[i] = j * 1024;
       } else {
         const int jw = j - nA, pb = jw >> 1;                   // present weight block pb
@@ -213,7 +204,7 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
     for (int r = t; r < MT; r += 256) {
       float v = 0.f;
       if (r < nvalid)
-        for (int c = 0; c < a.ss_parts; ++c) v += a.ssq[(slot0 + r) * a.ss_parts + c];
+        v = sum_row(a.ssq + (slot0 + r) * a.ss_parts, a.ss_parts);
       rowinv[r] = 1.f / sqrtf(v / (float)a.K + a.eps);
     }
   }
@@ -223,14 +214,6 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
   for (int i = 0; i < MBW; ++i)
 #pragma unroll
     for (int j = 0; j < NBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // QKV multiplies x g: the attention RMSNorm gain of this split's K range is staged in
-  // LDS before barrier 0 (at most kGainSteps K steps, checked at launch); 1/rms scales
-  // the summed rows in k_red_qkv
-  const __bf16 *gsl = reinterpret_cast<const __bf16 *>(rowinv);
-  if (MODE == G_QKV) {
-    for (int e = t; e < nk * KS / 8; e += 256)
-      reinterpret_cast<uint4 *>(rowinv)[e] = *reinterpret_cast<const uint4 *>(a.gain + k0 + 8 * e);
-  }
   // fragment (row l16, K sub-step s): 16-B chunk 4 s + g of the row, at its swizzled slot;
   // A and B use the same K order, so the products are those of the plain K order
   const uint32_t rowoff = l16 * RB;
@@ -248,16 +231,6 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
 #pragma unroll
       for (int j = 0; j < NBW; ++j)
         fb[s][j] = *reinterpret_cast<const bf16x8 *>(st + (S::AROWS + j * 16) * RB + rowoff + slot);
-    }
-    if (MODE == G_QKV) {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const bf16x8 gc = *reinterpret_cast<const bf16x8 *>(gsl + k * KS + (4 * s + g) * 8);
-#pragma unroll
-        for (int i = 0; i < MBW; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) fa[s][i][e] = (__bf16)((float)fa[s][i][e] * (float)gc[e]);
-      }
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -319,8 +292,7 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
 template <int MODE>
 __global__ __launch_bounds__(512) void k_wgemm(WArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
-  // SwiGLU: 1/rms per row; QKV: the attention RMSNorm gain of the split's K range
-  __shared__ __attribute__((aligned(16))) float rowinv[2 * MT];
+  __shared__ __attribute__((aligned(16))) float rowinv[MT];   // SwiGLU: 1/rms per row
   // split fastest: with 8 splits every split's workgroups share one XCD and its L2
   const int bid = blockIdx.x;
   const int sp = bid % a.splits;
@@ -399,8 +371,8 @@ __device__ float block_sum256(float v, float *red) {
   return res;
 }
 
-// Large-M path: one workgroup per slot, the gathered token's row of x, normalised and
-// scaled by the attention RMSNorm gain, as the QKV GEMM's bf16 operand.
+// One workgroup per slot: the gathered token's row of x, normalised and scaled by the
+// attention RMSNorm gain, as the QKV GEMM's bf16 operand.
 __global__ __launch_bounds__(256) void k_gather_norm(const uint16_t *__restrict__ x,
                                                      const uint16_t *__restrict__ gain,
                                                      const int32_t *__restrict__ idx,
@@ -441,134 +413,6 @@ __global__ __launch_bounds__(256) void k_gather_norm(const uint16_t *__restrict_
       *reinterpret_cast<U16x8 *>(xs + slot * d + c) = o;
     }
   }
-}
-
-// One workgroup per (slot, 1024 columns): split-K sum of (x g) W^T, scaled by the
-// token's 1/rms (from its row of x, read once per workgroup), plus the bias.  Queries
-// are rotated (rotate-half RoPE at the token's prompt position) in float32 before
-// their single rounding to bf16; a 1024-column block always holds whole heads, so
-// the partner dim of the rotation comes from LDS.  K and V rows go raw into the cache.
-template <int SPL>
-__global__ __launch_bounds__(256) void k_red_qkv(RedArgs r) {
-  __shared__ float qs[1024];
-  const long slot = blockIdx.x;
-  const int b = (int)(slot / r.N), j = (int)(slot - (long)b * r.N);
-  if (j >= n_valid(r.nrec, b, r.N)) return;
-  const int c0 = blockIdx.y * 1024;
-  const int c = c0 + threadIdx.x * 4;
-  const int tok = tok_of(r.idx, slot, r.N);
-  const bool incol = c < r.ncols;
-  const bool rot = c < r.qw;                      // query columns are rotated
-  const int half = r.hd / 2;
-  // Every load that depends only on the token goes out before the first use, so the
-  // workgroup waits one memory round trip instead of three: the split partials and
-  // the bias of the thread's 4 columns, its chunks of the input row (for 1/rms; d <=
-  // 8192: at most 4 chunks of 8 a thread) and the rotary pairs of its query dims.
-  // Threads past the columns or the row read an in-range element and never use it.
-  const float *pp = r.part + slot * r.ncols + (incol ? c : 0);
-  const long stride = r.rows * r.ncols;
-  float4 u[SPL];
-#pragma unroll
-  for (int s = 0; s < SPL; ++s)
-    u[s] = *reinterpret_cast<const float4 *>(pp + min(s, r.splits - 1) * stride);
-  const uint2 bb = *reinterpret_cast<const uint2 *>(r.bias + (incol ? c : 0));
-  const uint16_t *xr = r.x + ((long)b * r.N + tok) * r.d;
-  U16x8 xv[4];
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    const int cx = (it * 256 + threadIdx.x) * 8;
-    xv[it] = *reinterpret_cast<const U16x8 *>(xr + (cx < r.d ? cx : 0));
-  }
-  float2 cs[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int k = ((c + e) % r.hd) % half;       // rotary frequency pair
-    cs[e] = r.rope[rot ? (long)rope_pos(r.mr, r.qpos0 + tok, k) * half + k : 0L];
-  }
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-  for (int s = 0; s < SPL; ++s) {
-    const bool in = s < r.splits;
-    v.x += in ? u[s].x : 0.f;
-    v.y += in ? u[s].y : 0.f;
-    v.z += in ? u[s].z : 0.f;
-    v.w += in ? u[s].w : 0.f;
-  }
-  float ss = 0.f;
-#pragma unroll
-  for (int it = 0; it < 4; ++it) {
-    if ((it * 256 + (int)threadIdx.x) * 8 < r.d) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) ss = fmaf(bf2f(xv[it].v[e]), bf2f(xv[it].v[e]), ss);
-    }
-  }
-  const float inv = 1.f / sqrtf(block_sum256(ss, qs) / (float)r.d + r.eps);
-  float vv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (incol) {
-    const float bias[4] = {__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xFFFF0000u),
-                           __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xFFFF0000u)};
-    vv[0] = v.x; vv[1] = v.y; vv[2] = v.z; vv[3] = v.w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) vv[e] = fmaf(vv[e], inv, bias[e]);
-  }
-  if (c0 < r.qw) {   // uniform: the block's query columns are rotated
-    *reinterpret_cast<float4 *>(&qs[threadIdx.x * 4]) = make_float4(vv[0], vv[1], vv[2], vv[3]);
-    __syncthreads();
-    if (rot) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int d = (c + e) % r.hd;                 // dim within the head
-        const int lc = threadIdx.x * 4 + e;           // column within the block
-        vv[e] = d < half ? vv[e] * cs[e].x - qs[lc + half] * cs[e].y
-                         : vv[e] * cs[e].x + qs[lc - half] * cs[e].y;
-      }
-    }
-  }
-  if (!incol) return;
-  uint16_t o[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = f2bf(vv[e]);
-  uint16_t *dst;
-  if (c < r.qw)
-    dst = r.q + slot * r.qw + c;
-  else if (c < r.qw + r.kw)
-    dst = r.kc + ((long)b * r.S + pool_row(r.smap, b, r.S, r.cur_row0 + tok)) * r.kw + (c - r.qw);
-  else
-    dst = r.vc + ((long)b * r.S + pool_row(r.smap, b, r.S, r.cur_row0 + tok)) * r.kw +
-          (c - r.qw - r.kw);
-  *reinterpret_cast<uint2 *>(dst) = make_uint2(o[0] | ((uint32_t)o[1] << 16), o[2] | ((uint32_t)o[3] << 16));
-}
-
-template <int SPL>
-__global__ __launch_bounds__(256) void k_red_o(RedArgs r) {
-  __shared__ float red[256];
-  const long slot = blockIdx.x;
-  const int b = (int)(slot / r.N), j = (int)(slot - (long)b * r.N);
-  if (j >= n_valid(r.nrec, b, r.N)) return;
-  const int c = blockIdx.y * 1024 + threadIdx.x * 4;
-  const int tok = tok_of(r.idx, slot, r.N);
-  float ss = 0.f;
-  if (c < r.d) {
-    const float4 v = sum_parts<SPL>(r, slot, c);
-    const uint2 xb = *reinterpret_cast<const uint2 *>(r.x + ((long)b * r.N + tok) * r.d + c);
-    float4 h;
-    h.x = v.x + __uint_as_float(xb.x << 16);
-    h.y = v.y + __uint_as_float(xb.x & 0xFFFF0000u);
-    h.z = v.z + __uint_as_float(xb.y << 16);
-    h.w = v.w + __uint_as_float(xb.y & 0xFFFF0000u);
-    *reinterpret_cast<float4 *>(r.h1 + slot * r.d + c) = h;
-    // the SwiGLU operand carries the MLP RMSNorm gain; 1/rms is applied to its sums
-    const uint2 gb = *reinterpret_cast<const uint2 *>(r.gain + c);
-    const uint16_t b0 = f2bf(h.x * __uint_as_float(gb.x << 16));
-    const uint16_t b1 = f2bf(h.y * __uint_as_float(gb.x & 0xFFFF0000u));
-    const uint16_t b2 = f2bf(h.z * __uint_as_float(gb.y << 16));
-    const uint16_t b3 = f2bf(h.w * __uint_as_float(gb.y & 0xFFFF0000u));
-    *reinterpret_cast<uint2 *>(r.hb + slot * r.d + c) =
-        make_uint2(b0 | ((uint32_t)b1 << 16), b2 | ((uint32_t)b3 << 16));
-    ss = h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w;
-  }
-  ss = block_sum256(ss, red);
-  if (threadIdx.x == 0) r.ssq[slot * gridDim.y + blockIdx.y] = ss;
 }
 
 template <int SPL>
@@ -1753,12 +1597,6 @@ fc_status run_wgemm(fc_ctx *ctx, hipStream_t st, const char *name, WArgs &g, int
     splits = std::min(splits, std::max(1, ksteps / 4));
     while (splits > 1 && (size_t)splits * g.rows * g.Nout > ctx->part_elems) --splits;
   }
-  if (MODE == G_QKV && (ksteps + splits - 1) / splits > kGainSteps) {
-    // the gain slice of a split's K range must fit in LDS
-    splits = (ksteps + kGainSteps - 1) / kGainSteps;
-    if (splits > kMaxSplits || (size_t)splits * g.rows * g.Nout > ctx->part_elems)
-      return fail(FC_ERR_UNSUPPORTED, "%s: K %d needs more than %d splits", name, g.K, kMaxSplits);
-  }
   g.ksteps = (ksteps + splits - 1) / splits;
   g.splits = (ksteps + g.ksteps - 1) / g.ksteps;
   if (MODE != G_GU && (size_t)g.splits * g.rows * g.Nout > ctx->part_elems)
@@ -1820,19 +1658,44 @@ fc_status run_mgemm(fc_ctx *ctx, hipStream_t st, const char *name, MArgs &g, int
 }  // namespace
 
 namespace {
-template <int SPL>
-void launch_red(int which, dim3 grid, hipStream_t st, const RedArgs &r) {
-  if (which == 0) hipLaunchKernelGGL(k_red_qkv<SPL>, grid, dim3(256), 0, st, r);
-  else if (which == 1) hipLaunchKernelGGL(k_red_o<SPL>, grid, dim3(256), 0, st, r);
-  else hipLaunchKernelGGL(k_red_down<SPL>, grid, dim3(256), 0, st, r);
+void run_red_down(dim3 grid, hipStream_t st, const RedArgs &r) {
+  if (r.splits <= 1) hipLaunchKernelGGL(k_red_down<1>, grid, dim3(256), 0, st, r);
+  else if (r.splits <= 2) hipLaunchKernelGGL(k_red_down<2>, grid, dim3(256), 0, st, r);
+  else if (r.splits <= 4) hipLaunchKernelGGL(k_red_down<4>, grid, dim3(256), 0, st, r);
+  else if (r.splits <= 8) hipLaunchKernelGGL(k_red_down<8>, grid, dim3(256), 0, st, r);
+  else hipLaunchKernelGGL(k_red_down<16>, grid, dim3(256), 0, st, r);
 }
-// which: 0 QKV, 1 O, 2 down
-void run_red(int which, dim3 grid, hipStream_t st, const RedArgs &r) {
-  if (r.splits <= 1) launch_red<1>(which, grid, st, r);
-  else if (r.splits <= 2) launch_red<2>(which, grid, st, r);
-  else if (r.splits <= 4) launch_red<4>(which, grid, st, r);
-  else if (r.splits <= 8) launch_red<8>(which, grid, st, r);
-  else launch_red<16>(which, grid, st, r);
+
+// A row GEMM over the items of a layer, kMMaxItems at a time (N slots each; null rows: all).
+template <int MODE>
+fc_status run_layer_rows(fc_ctx *ctx, hipStream_t st, const char *name, RowGemm a, int B,
+                         const int32_t *rows) {
+  const long N = a.g.N;
+  for (int b0 = 0; b0 < B; b0 += kMMaxItems) {
+    a.B = std::min(kMMaxItems, B - b0);
+    const fc_status rc = run_row_gemm<MODE>(ctx, st, name, a, rows);
+    if (rc != FC_OK) return rc;
+    const long n = kMMaxItems * N;
+    a.A += n * a.K;
+    if (a.idx) a.idx += n;
+    if (rows) rows += kMMaxItems;
+    if (MODE == L_QKV) {
+      a.q += n * a.qw;
+      a.kc += (long)kMMaxItems * a.S * a.kw;
+      a.vc += (long)kMMaxItems * a.S * a.kw;
+      if (a.smap) a.smap += (long)kMMaxItems * a.S;
+    } else {
+      a.h1 += n * a.g.d;
+      if (MODE == L_O) {
+        a.x += n * a.g.d;
+        a.hb += n * a.g.d;
+        a.ssq += n * a.parts;
+      } else {
+        a.y += n * a.g.d;
+      }
+    }
+  }
+  return FC_OK;
 }
 }  // namespace
 
@@ -1856,8 +1719,7 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
   if (trail) idx = nrec = nullptr;
   const int want = std::max(ctx->num_cus, 1);
   // thousands of gathered rows (several batch items of large frames) make the
-  // projections compute bound: square MFMA tiles with fused epilogues instead of the
-  // weight-streaming kernels and their split-K reductions
+  // projections compute bound: 256 x 256 tiles instead of the few-row kernels
   const bool big = !trail && rows >= kBigRows && (hd == 64 || hd == 128) && B <= kMMaxItems;
 
   // RoPE table for (hd, theta) over the cache length (rebuilt only when they change)
@@ -1886,36 +1748,46 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
   }
   r.mr = mr;
   fc_status rc;
+  // few-row path: the operands of the projections with fused epilogues
+  RowGemm p{};
+  p.cus = want;
+  p.idx = idx;
+  p.g.N = p.g.Np = N;
+  p.g.m = p.g.mm = 1;
+  p.g.d = d;
+  p.g.hd = hd;
+  p.rope = ctx->rope;
+  p.qw = r.qw; p.kw = r.kw;
+  p.q = ctx->qbuf; p.kc = kv.k; p.vc = kv.v;
+  p.smap = kv.slot_map;
+  p.S = S; p.cur_row0 = cur_row0; p.qpos0 = qpos0;
+  p.mr = mr;
+  p.x = x_cur; p.g2 = L.g_mlp;
+  p.h1 = ctx->h1; p.hb = ctx->hb; p.y = y_cur;
+  // sums of squares per 64 columns, beside no partial sums that are in use at the time
+  p.ssq = ctx->part;
+  p.parts = d / kRowSsqCols;
 
-  // 1. QKV of the recomputed rows.  Large-M path: gather + RMSNorm of the rows, then a
-  //    GEMM whose epilogue adds the bias, rotates q and scatters raw k, v into the
-  //    current frame's cache rows.  Few-row path: the GEMM gathers the rows of x by
-  //    token id itself and multiplies x g; the reduction scales by 1/rms, adds the bias,
-  //    stores rotated q and scatters raw k, v
+  // 1. QKV of the recomputed rows: gather + RMSNorm of the rows, then a GEMM whose
+  //    epilogue adds the bias, rotates q and scatters raw k, v into the current frame's
+  //    cache rows
   {
-    r.ncols = qkv;
-    r.bias = L.b_qkv; r.q = ctx->qbuf; r.kc = kv.k; r.vc = kv.v; r.smap = kv.slot_map;
+    {
+      ProfScope ps(ctx, st, "fc_gather_norm");
+      hipLaunchKernelGGL(k_gather_norm, dim3((unsigned)rows), dim3(256), 0, st, x_cur, L.g_attn,
+                         idx, nrec, N, d, L.rms_eps, ctx->hb);
+      FC_LAUNCH_OK(st, "k_gather_norm");
+    }
     if (big) {
-      {
-        ProfScope ps(ctx, st, "fc_gather_norm");
-        hipLaunchKernelGGL(k_gather_norm, dim3((unsigned)rows), dim3(256), 0, st, x_cur, L.g_attn,
-                           idx, nrec, N, d, L.rms_eps, ctx->hb);
-        FC_LAUNCH_OK(st, "k_gather_norm");
-      }
+      r.bias = L.b_qkv; r.q = ctx->qbuf; r.kc = kv.k; r.vc = kv.v; r.smap = kv.slot_map;
       MArgs g{};
       g.A = ctx->hb; g.W0 = L.w_qkv;
       g.K = d; g.Nout = qkv; g.N = N; g.r = r;
       if ((rc = run_mgemm<G_QKV>(ctx, st, "fc_mgemm_qkv", g, B)) != FC_OK) return rc;
     } else {
-      WArgs g{};
-      g.A = x_cur; g.gather = 1; g.gain = L.g_attn; g.W0 = L.w_qkv;
-      g.K = d; g.Nout = qkv; g.N = N; g.idx = idx; g.nrec = nrec;
-      g.part = ctx->part; g.rows = rows; g.eps = L.rms_eps;
-      if ((rc = run_wgemm<G_QKV>(ctx, st, "fc_gemm_qkv", g, B)) != FC_OK) return rc;
-      r.splits = g.splits;
-      ProfScope ps(ctx, st, "fc_red_qkv");
-      run_red(0, dim3((unsigned)rows, (qkv + 1023) / 1024), st, r);
-      FC_LAUNCH_OK(st, "k_red_qkv");
+      p.A = ctx->hb; p.W = L.w_qkv; p.bias = L.b_qkv;
+      p.K = d; p.cols = qkv;
+      if ((rc = run_layer_rows<L_QKV>(ctx, st, "fc_gemm_qkv", p, B, nrec)) != FC_OK) return rc;
     }
   }
 
@@ -2010,26 +1882,19 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
     }
   }
 
-  // 3. O projection; reduction adds the residual -> h1 (float32) and its bf16 copy
-  r.ncols = d; r.h1 = ctx->h1; r.hb = ctx->hb; r.ssq = ctx->ssq; r.gain = L.g_mlp; r.y = y_cur;
-  // sums of squares of h1 per row: per 1024 columns from the O reduction, per 256
-  // columns from the large-M epilogue
-  const int ss_parts = big ? (d + kMSsqCols - 1) / kMSsqCols : (d + 1023) / 1024;
+  // 3. O projection, with the residual -> h1 (float32), the MLP operand bf16(h1 * g_mlp)
+  //    and the sums of squares of h1 per row: per 256 columns in the large-M epilogue
+  r.h1 = ctx->h1; r.hb = ctx->hb; r.ssq = ctx->ssq; r.gain = L.g_mlp; r.y = y_cur;
+  const int ss_parts = big ? (d + kMSsqCols - 1) / kMSsqCols : p.parts;
   if (big) {
     MArgs g{};
     g.A = ctx->attn; g.W0 = L.w_o;
     g.K = nh * hd; g.Nout = d; g.N = N; g.ss_parts = ss_parts; g.r = r;
     if ((rc = run_mgemm<G_O>(ctx, st, "fc_mgemm_o", g, B)) != FC_OK) return rc;
   } else {
-    WArgs g{};
-    g.A = ctx->attn; g.W0 = L.w_o;
-    g.K = nh * hd; g.Nout = d; g.N = N; g.idx = idx; g.nrec = nrec;
-    g.part = ctx->part; g.rows = rows;
-    if ((rc = run_wgemm<G_O>(ctx, st, "fc_gemm_o", g, B)) != FC_OK) return rc;
-    r.splits = g.splits;
-    ProfScope ps(ctx, st, "fc_red_o");
-    run_red(1, dim3((unsigned)rows, (d + 1023) / 1024), st, r);
-    FC_LAUNCH_OK(st, "k_red_o");
+    p.A = ctx->attn; p.W = L.w_o;
+    p.K = nh * hd; p.cols = d;
+    if ((rc = run_layer_rows<L_O>(ctx, st, "fc_gemm_o", p, B, nrec)) != FC_OK) return rc;
   }
 
   // 4. gate/up on bf16(h1 * g_mlp); 1/rms from the sums of squares is applied to both
@@ -2042,9 +1907,9 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
   } else {
     WArgs g{};
     g.A = ctx->hb; g.W0 = L.w_gate; g.W1 = L.w_up;
-    g.K = d; g.Nout = ffn; g.N = N; g.idx = idx; g.nrec = nrec;
+    g.K = d; g.Nout = ffn; g.N = N; g.nrec = nrec;
     g.rows = rows; g.act = ctx->act; g.eps = L.rms_eps;
-    g.ssq = ctx->ssq; g.ss_parts = ss_parts;
+    g.ssq = p.ssq; g.ss_parts = ss_parts;
     if ((rc = run_wgemm<G_GU>(ctx, st, "fc_gemm_gateup", g, B)) != FC_OK) return rc;
   }
 
@@ -2054,15 +1919,19 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
     g.A = ctx->act; g.W0 = L.w_down;
     g.K = ffn; g.Nout = d; g.N = N; g.r = r;
     if ((rc = run_mgemm<G_DOWN>(ctx, st, "fc_mgemm_down", g, B)) != FC_OK) return rc;
+  } else if (row_gemm_pays(ffn, B * ((N + MT - 1L) / MT))) {
+    p.A = ctx->act; p.W = L.w_down;
+    p.K = ffn; p.cols = d;
+    if ((rc = run_layer_rows<L_DOWN>(ctx, st, "fc_gemm_down", p, B, nrec)) != FC_OK) return rc;
   } else {
     WArgs g{};
     g.A = ctx->act; g.W0 = L.w_down;
-    g.K = ffn; g.Nout = d; g.N = N; g.idx = idx; g.nrec = nrec;
+    g.K = ffn; g.Nout = d; g.N = N; g.nrec = nrec;
     g.part = ctx->part; g.rows = rows;
     if ((rc = run_wgemm<G_DOWN>(ctx, st, "fc_gemm_down", g, B)) != FC_OK) return rc;
-    r.splits = g.splits;
+    r.splits = g.splits; r.ncols = d;
     ProfScope ps(ctx, st, "fc_red_down");
-    run_red(2, dim3((unsigned)rows, (d + 1023) / 1024), st, r);
+    run_red_down(dim3((unsigned)rows, (d + 1023) / 1024), st, r);
     FC_LAUNCH_OK(st, "k_red_down");
   }
   return FC_OK;
@@ -2075,7 +1944,7 @@ fc_status run_plain_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const ui
   g.A = A; g.W0 = W;
   g.K = K; g.Nout = Nout; g.N = N; g.nrec = nrec;
   g.part = part; g.rows = (long)B * N;
-  fc_status rc = run_wgemm<G_O>(ctx, st, name, g, B);
+  fc_status rc = run_wgemm<G_DOWN>(ctx, st, name, g, B);
   *splits = g.splits;
   return rc;
 }

@@ -10,16 +10,16 @@
 //   k_vit_gather_norm  one workgroup per slot: the patch row of x, RMSNorm (g1) as the
 //                      bf16 operand of the QKV GEMM; the item's row count; the rotary table;
 //                      the cached keys rotated, where a window has more than 64 keys.
-//   k_vit_gemm<V_QKV>  + bias; q rotated at the patch position (bf16, compact), raw k and v
+//   k_row_gemm<V_QKV>  + bias; q rotated at the patch position (bf16, compact), raw k and v
 //                      into the cache at the patch row.
 //   k_vit_attn         one workgroup per (window, query chunk, head) or, with full
 //                      attention, per (query chunk, head): the chunk's queries against the
 //                      window's (the frame's) keys in blocks, S^T = K Q^T and O^T = V^T P^T
 //                      on bf16 MFMAs, online softmax in fp32.
-//   k_vit_gemm<V_O>    + bias + residual -> h1 (fp32), bf16(h1 g2) and the row's sums of
+//   k_row_gemm<V_O>    + bias + residual -> h1 (fp32), bf16(h1 g2) and the row's sums of
 //                      squares by 64 columns.
-//   k_vit_gemm<V_GU>   times 1/rms(h1), + biases, SiLU(g) u -> bf16.
-//   k_vit_gemm<V_DOWN> + bias + h1 -> the slot's output row of y (bf16).
+//   k_row_gemm<V_GU>   times 1/rms(h1), + biases, SiLU(g) u -> bf16.
+//   k_row_gemm<V_DOWN> + bias + h1 -> the slot's output row of y (bf16).
 //
 // The 2-D rotary angle of dim pair i (i < hd/2) of a patch at (row, col) is
 // row * f_i for i < hd/4 and col * f_(i - hd/4) otherwise, f_k = theta^(-2k / (hd/2));
@@ -32,6 +32,7 @@
 
 #include "fc_internal.h"
 #include "gemm_dev.h"
+#include "rowgemm.h"
 
 namespace fc {
 namespace {
@@ -39,26 +40,6 @@ namespace {
 constexpr int kVitThreads = 256;
 constexpr int kVitQ = 64;            // queries per attention workgroup
 
-__device__ __forceinline__ float bf2f_v(uint16_t u) { return __uint_as_float((uint32_t)u << 16); }
-__device__ __forceinline__ uint16_t f2bf_v(float f) {
-  const uint32_t u = __float_as_uint(f);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-
-struct VitGeo {
-  int N, m, mm, Np, gh, gw, d, H, hd, win;
-};
-
-// slot j of an item -> patch row (idx: the item's token ids)
-__device__ __forceinline__ int slot_patch(const int32_t *idx, const VitGeo &g, int b, int j) {
-  const int t = min(max(idx[(long)b * g.N + j / g.mm], 0), g.N - 1);
-  return t * g.mm + j % g.mm;
-}
-__device__ __forceinline__ void patch_pos(const VitGeo &g, int p, int &pr, int &pc) {
-  const int t = p / g.mm, sub = p - t * g.mm;
-  pr = (t / g.gw) * g.m + sub / g.m;
-  pc = (t % g.gw) * g.m + sub % g.m;
-}
 __device__ __forceinline__ int n_rows(const int32_t *nrec, const VitGeo &g, int b) {
   return min(max(nrec[b], 0), g.N) * g.mm;
 }
@@ -104,16 +85,6 @@ __device__ __forceinline__ float4 sum_parts4(const float *__restrict__ part, int
                                              long s, int nc, int c) {
   return sum_splits4<SPL>(part + s * nc + c, rows * nc, splits);
 }
-__device__ __forceinline__ float4 bf4(const uint16_t *p) {
-  const uint2 u = *reinterpret_cast<const uint2 *>(p);
-  return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
-                     __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
-}
-__device__ __forceinline__ void st_bf4(uint16_t *p, float a, float b, float c, float d) {
-  *reinterpret_cast<uint2 *>(p) = make_uint2(f2bf_v(a) | ((uint32_t)f2bf_v(b) << 16),
-                                             f2bf_v(c) | ((uint32_t)f2bf_v(d) << 16));
-}
-
 __device__ __forceinline__ void ld_bf8(const uint16_t *p, float *v) {
   const uint4 u = *reinterpret_cast<const uint4 *>(p);
   const uint32_t w[4] = {u.x, u.y, u.z, u.w};
@@ -126,7 +97,7 @@ __device__ __forceinline__ void ld_bf8(const uint16_t *p, float *v) {
 __device__ __forceinline__ void st_bf8(uint16_t *p, const float *v) {
   uint32_t w[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = f2bf_v(v[2 * i]) | ((uint32_t)f2bf_v(v[2 * i + 1]) << 16);
+  for (int i = 0; i < 4; ++i) w[i] = f2bf(v[2 * i]) | ((uint32_t)f2bf(v[2 * i + 1]) << 16);
   *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
@@ -546,375 +517,6 @@ __global__ __launch_bounds__(512) void k_vit_attn(
   }
 }
 
-// ------------------------------------------------------------------------------ GEMMs
-// C[rows][cols] = A[rows][K] W[cols][K]^T over the recomputed rows packed across items, with
-// the projection's epilogue: one workgroup per TM x TN tile (TN staged weight rows), the whole
-// K range, no partial sums.  A projection of a frame has a few hundred to a few thousand rows,
-// so what bounds a tile is the load path of its CU (TM + TN rows of 128 B a K step), not its
-// MFMAs: the tile is chosen on the device, where the row count is known, as the one whose CUs
-// load least (vit_tile).
-//   * NST stages of (TM + TN) rows rotate in LDS, 64 K values (a 128-B line) a row, 16-B
-//     chunks XOR-swizzled by (row >> 1) & 7.  Waves 4-7 only issue the DMAs (a DMA holds its
-//     wave at issue): after barrier k those of step k + NST - 1, into the stage of step k - 1.
-//     Waves 0-3 multiply, a quarter of the tile each, and read the fragments of the next half
-//     step while they multiply this one, across the barrier too.  (All eight waves loading and
-//     multiplying, with or without the halves of the workgroup in alternating phases, was up
-//     to 30 % slower: the DMAs keep the MFMAs waiting.)
-//   * The accumulators go through LDS as whole rows, so that every global access of the
-//     epilogue is a piece of a row: V_QKV adds the bias, rotates q and scatters raw k and v
-//     into the cache; V_O adds bias and residual and writes h1, the MLP operand bf16(h1 g2)
-//     and the row's sums of squares per 64 columns; V_GU applies 1/rms, adds the biases and
-//     writes SiLU(g) u; V_DOWN adds bias and h1 and scatters the output rows.
-//   * V_QKV stages a column beside its rotary partner half a head away (V_GU: a gate beside
-//     its up row): staged rows [0, TN / 2) are columns, [TN / 2, TN) their partners.
-//   * M tiles of one column tile are consecutive, so each XCD reads its own share of the
-//     weights once.
-// Measured on the Qwen2.5-VL block (d 1280, MLP 3456), us, against 256 x 256 tiles in up to 8
-// K-range parts with a reduction kernel each: QKV 23 + 15 -> 18.5, O 15 + 9 -> 14, gate/up
-// 28 + 14 -> 26, down 21 + 9 -> 21 at 1024 rows; the whole windowed block 157 -> 91 at 1024
-// rows, 129 -> 78 at 512 and 89 -> 54 at 104 rows (there against the weight-streaming GEMM
-// and its reductions).  The DMA pattern alone takes 7.3 us for QKV (37 B a clock and CU); LDS
-// traffic (operands written once and read twice), about 3 us before the first step is staged
-// and 2 us of epilogue make up the rest.
-enum { V_QKV = 0, V_O = 1, V_GU = 2, V_DOWN = 3 };
-constexpr int kVitLds = 150 * 1024;
-constexpr int kVitSsqCols = 64;         // columns per partial sum of squares of h1
-
-struct VitGemm {
-  const uint16_t *A, *W, *bias;
-  int K, cols;                          // cols: weight rows staged in all (V_GU: 2 f)
-  int B, cus;
-  const int32_t *idx;
-  VitGeo g;
-  const float2 *rope;
-  uint16_t *q, *kc, *vc, *krot;         // V_QKV
-  const uint16_t *x, *g2;               // V_O
-  float *h1, *ssq;                      // V_O (V_GU reads ssq, V_DOWN h1)
-  uint16_t *hb;                         // V_O
-  uint16_t *act;                        // V_GU
-  uint16_t *y;                          // V_DOWN
-  int parts;                            // sums of squares per row
-  float eps;
-};
-
-struct VitTile {
-  int v, tiles;                         // variant, tiles of all rows
-};
-constexpr int kVitTM[4] = {128, 64, 64, 32}, kVitTN[4] = {128, 128, 64, 64};
-constexpr int kVitGuTM[4] = {128, 128, 64, 32}, kVitGuTN[4] = {256, 128, 128, 64};
-// The tile for `rows` rows: least rows loaded per CU, (TM + TN) times the rounds of one
-// workgroup per CU (a K step of a 64 x 64 tile takes 0.2 us, of a 128 x 128 tile 0.5 us).  Host
-// and device take the same decision.
-__host__ __device__ inline VitTile vit_tile(bool gu, int rows, int cols, int cus) {
-  VitTile best{0, 0};
-  int least = 0;
-  for (int v = 0; v < 4; ++v) {
-    const int tm = gu ? kVitGuTM[v] : kVitTM[v], tn = gu ? kVitGuTN[v] : kVitTN[v];
-    const int tiles = ((rows + tm - 1) / tm) * ((cols + tn - 1) / tn);
-    const int cost = (tiles + cus - 1) / cus * (tm + tn);
-    if (v == 0 || cost < least) {
-      best = VitTile{v, tiles};
-      least = cost;
-    }
-  }
-  return best;
-}
-
-__device__ __forceinline__ long row_slot(const int *pre, int B, int N, int p, int &b) {
-  if (B > 1) return packed_slot(pre, B, N, p, b);
-  b = 0;
-  return p;
-}
-
-template <int MODE, int TM, int TN>
-__device__ __forceinline__ void vit_gemm_tile(const VitGemm &a, unsigned char *lds, const int *pre,
-                                              int *rslot, int *rpatch, int *rpos, float *rinv,
-                                              int row0, int nvalid, int nt) {
-  constexpr int STAGE = (TM + TN) * RB;
-  constexpr int NST = kVitLds / STAGE > 8 ? 8 : kVitLds / STAGE;
-  constexpr int NI = (TM + TN) / 8;               // DMA instructions per step
-  constexpr int L = NI / 4;                       // of each loader wave
-  constexpr int MBW = TM / 32, NBW = TN / 32;     // 16-row blocks of a wave's quarter
-  constexpr bool PAIR = MODE == V_QKV || MODE == V_GU;
-  static_assert(NST >= 3 && NI % 4 == 0 && (NST - 1) * L < 64, "stages");
-  const int t = threadIdx.x, lane = t & 63;
-  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const VitGeo &g = a.g;
-  const int nk = a.K / KS;
-  // column of staged row r (clamped: past the last column nothing is stored)
-  auto column = [&](int r) {
-    if (MODE == V_QKV) {
-      const int half = g.hd / 2, p = min(nt * (TN / 2) + r % (TN / 2), a.cols / 2 - 1);
-      const int h = p / half;
-      return h * g.hd + (p - h * half) + (r >= TN / 2 ? half : 0);
-    }
-    if (MODE == V_GU)
-      return min(nt * (TN / 2) + r % (TN / 2), a.cols / 2 - 1) + (r >= TN / 2 ? a.cols / 2 : 0);
-    return min(nt * TN + r, a.cols - 1);
-  };
-  constexpr int TP = TN + 4;                      // floats per row of the epilogue tile
-  static_assert(TM * TP * 4 <= kVitLds, "the tile fits");
-  float *T = reinterpret_cast<float *>(lds);
-  if (w >= 4) {
-    // ------------------------------------------------------------------ loader waves
-    const uint16_t *gp[L];
-    const int rsub = lane >> 3, ch = lane & 7;
-#pragma unroll
-    for (int i = 0; i < L; ++i) {
-      const int r = (w - 4 + 4 * i) * 8 + rsub;   // row of the stage
-      const int cs = (ch ^ swz8(r)) * 8;
-      if (r < TM) {
-        int ib;
-        gp[i] = a.A + row_slot(pre, a.B, g.Np, row0 + min(r, nvalid - 1), ib) * a.K + cs;
-      } else {
-        gp[i] = a.W + (long)column(r - TM) * a.K + cs;
-      }
-    }
-    const uint32_t lbase = lds_addr(lds) + (w - 4) * 1024;
-    auto issue = [&](int k) {
-      const uint32_t st = lbase + (k % NST) * STAGE;
-#pragma unroll
-      for (int i = 0; i < L; ++i) dma16(gp[i] + k * KS, st + i * 4096);
-    };
-    for (int k = 0; k < NST - 1 && k < nk; ++k) issue(k);
-    for (int k = 0; k < nk; ++k) {
-      if (k + NST - 1 <= nk) wait_vm<(NST - 2) * L>();     // this wave's share of step k
-      else wait_vm_rt((nk - 1 - k) * L);
-      lds_barrier();                                       // barrier k: step k staged, k - 1 read
-      if (k + NST - 1 < nk) issue(k + NST - 1);
-    }
-    lds_barrier();                                         // barrier nk: the stages are free
-  } else {
-    // -------------------------------------------------------------------- MFMA waves
-    // the tile's rows: slot, patch row (b Np + patch) and, for V_GU, 1/rms of h1
-    if (t < TM) {
-      int b = 0;
-      const long sl = row_slot(pre, a.B, g.Np, row0 + min(t, nvalid - 1), b);
-      rslot[t] = (int)sl;
-      if (MODE != V_GU) {
-        const int p = slot_patch(a.idx, g, b, (int)(sl - (long)b * g.Np));
-        rpatch[t] = b * g.Np + p;
-        if (MODE == V_QKV) {
-          int pr, pc;
-          patch_pos(g, p, pr, pc);
-          rpos[t] = pr << 16 | pc;
-        }
-      }
-      if (MODE == V_GU) {
-        float v = 0.f;
-        for (int c = 0; c < a.parts; ++c) v += a.ssq[sl * a.parts + c];
-        rinv[t] = 1.f / sqrtf(v / (float)g.d + a.eps);
-      }
-    }
-    f32x4 acc[MBW][NBW];
-#pragma unroll
-    for (int i = 0; i < MBW; ++i)
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int l16 = lane & 15, gq = lane >> 4, wm = w & 1, wn = w >> 1;
-    const int sw = swz8(l16);
-    const uint32_t aoff = (uint32_t)((wm * (TM / 2) + l16) * RB);
-    const uint32_t boff = (uint32_t)((TM + wn * (TN / 2) + l16) * RB);
-    auto rd = [&](int k, int s, bf16x8 (&fa)[MBW], bf16x8 (&fb)[NBW]) __attribute__((always_inline)) {
-      const unsigned char *st = lds + (k % NST) * STAGE + (((4 * s + gq) ^ sw) << 4);
-#pragma unroll
-      for (int i = 0; i < MBW; ++i) fa[i] = *reinterpret_cast<const bf16x8 *>(st + aoff + i * 16 * RB);
-#pragma unroll
-      for (int j = 0; j < NBW; ++j) fb[j] = *reinterpret_cast<const bf16x8 *>(st + boff + j * 16 * RB);
-    };
-    auto mul = [&](const bf16x8 (&fa)[MBW], const bf16x8 (&fb)[NBW]) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < MBW; ++i)
-#pragma unroll
-        for (int j = 0; j < NBW; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    };
-    // the fragments of the next half step are read while this one's are multiplied, across
-    // the barrier too
-    bf16x8 fa0[MBW], fb0[NBW], fa1[MBW], fb1[NBW];
-    lds_barrier();                                         // barrier 0
-    rd(0, 0, fa0, fb0);
-    for (int k = 0; k < nk; ++k) {
-      rd(k, 1, fa1, fb1);
-      mul(fa0, fb0);
-      lds_barrier();                                       // barrier k + 1
-      if (k + 1 < nk) rd(k + 1, 0, fa0, fb0);
-      mul(fa1, fb1);
-    }
-    // lane holds column l16 and rows 4 gq + e of each 16-row block
-#pragma unroll
-    for (int i = 0; i < MBW; ++i)
-#pragma unroll
-      for (int j = 0; j < NBW; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          T[(wm * (TM / 2) + i * 16 + 4 * gq + e) * TP + wn * (TN / 2) + j * 16 + l16] = acc[i][j][e];
-  }
-  lds_barrier();
-  // A thread has 4 columns (PAIR: and their 4 partners) of every (512 / QPR)-th row, so what
-  // depends on the columns is found once, and a turn's loads go out for all rows first.
-  constexpr int QPR = (PAIR ? TN / 2 : TN) / 4, RSTEP = 512 / QPR, IT = (TM + RSTEP - 1) / RSTEP;
-  static_assert(512 % QPR == 0, "fixed columns");
-  const int r0 = t / QPR, c4 = (t % QPR) * 4;
-  if (PAIR) {
-    const int p = nt * (TN / 2) + c4;
-    if (p >= a.cols / 2) return;
-    const int c0 = column(c4), c1 = column(TN / 2 + c4);
-    const float4 b0 = bf4(a.bias + c0), b1 = bf4(a.bias + c1);
-    const float bb0[4] = {b0.x, b0.y, b0.z, b0.w}, bb1[4] = {b1.x, b1.y, b1.z, b1.w};
-    const bool rot = MODE == V_QKV && c0 < (a.krot ? 2 : 1) * g.d;
-    // rotary pairs c0 % hd .. + 3: the first quarter of a head turns by the patch row, the
-    // second by its column (four pairs may span both)
-    const int quarter = g.hd / 4, pair = c0 % g.hd;
-    const bool isq = c0 < g.d;
-    float2 cs[IT][4];
-    if (rot) {
-#pragma unroll
-      for (int n = 0; n < IT; ++n) {
-        const int pos = rpos[min(r0 + n * RSTEP, TM - 1)], pr = pos >> 16, pc = pos & 0xFFFF;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool lo = pair + i < quarter;
-          cs[n][i] = a.rope[(lo ? pr : pc) * 32 + pair + i - (lo ? 0 : quarter)];
-        }
-      }
-    }
-    uint16_t *kv = c0 < 2 * g.d ? a.kc - g.d : a.vc - 2 * g.d;
-#pragma unroll
-    for (int n = 0; n < IT; ++n) {
-      const int r = r0 + n * RSTEP;
-      if (r >= nvalid) break;
-      const float4 v = *reinterpret_cast<const float4 *>(T + r * TP + c4);
-      const float4 u = *reinterpret_cast<const float4 *>(T + r * TP + TN / 2 + c4);
-      const float v4[4] = {v.x, v.y, v.z, v.w}, u4[4] = {u.x, u.y, u.z, u.w};
-      float x0[4], x1[4];
-      if (MODE == V_GU) {
-        const float inv = rinv[r];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float gv = v4[i] * inv + bb0[i], uv = u4[i] * inv + bb1[i];
-          x0[i] = gv * __builtin_amdgcn_rcpf(1.f + __expf(-gv)) * uv;
-        }
-        st_bf4(a.act + (long)rslot[r] * (a.cols / 2) + p, x0[0], x0[1], x0[2], x0[3]);
-      } else {
-        // raw keys and values go to the cache, rotated queries and keys to the attention
-        float y0[4], y1[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x0[i] = v4[i] + bb0[i];
-          x1[i] = u4[i] + bb1[i];
-          if (rot) {
-            y0[i] = x0[i] * cs[n][i].x - x1[i] * cs[n][i].y;
-            y1[i] = x1[i] * cs[n][i].x + x0[i] * cs[n][i].y;
-          }
-        }
-        if (!isq) {
-          uint16_t *dst = kv + (long)rpatch[r] * g.d;
-          st_bf4(dst + c0, x0[0], x0[1], x0[2], x0[3]);
-          st_bf4(dst + c1, x1[0], x1[1], x1[2], x1[3]);
-        }
-        if (rot) {
-          uint16_t *dst = isq ? a.q + (long)rslot[r] * g.d : a.krot - g.d + (long)rpatch[r] * g.d;
-          st_bf4(dst + c0, y0[0], y0[1], y0[2], y0[3]);
-          st_bf4(dst + c1, y1[0], y1[1], y1[2], y1[3]);
-        }
-      }
-    }
-  } else {
-    const int c = nt * TN + c4;
-    const bool cv = c < a.cols;
-    const int cc = cv ? c : 0;
-    const float4 bb = bf4(a.bias + cc);
-    const float4 gn = MODE == V_O ? bf4(a.g2 + cc) : make_float4(0.f, 0.f, 0.f, 0.f);
-    uint2 xr[MODE == V_O ? IT : 1];
-    float4 hr[MODE == V_DOWN ? IT : 1];
-#pragma unroll
-    for (int n = 0; n < IT; ++n) {
-      const int r = min(r0 + n * RSTEP, nvalid - 1);
-      if (MODE == V_O) xr[n] = *reinterpret_cast<const uint2 *>(a.x + (long)rpatch[r] * g.d + cc);
-      if (MODE == V_DOWN) hr[n] = *reinterpret_cast<const float4 *>(a.h1 + (long)rslot[r] * g.d + cc);
-    }
-#pragma unroll
-    for (int n = 0; n < IT; ++n) {
-      const int r = r0 + n * RSTEP;
-      const bool rv = r < nvalid;
-      float ss = 0.f;
-      if (rv && cv) {
-        const long slot = rslot[r];
-        const float4 v = *reinterpret_cast<const float4 *>(T + r * TP + c4);
-        if (MODE == V_O) {
-          const float4 xv = unpack_bf16x4(xr[n]);
-          const float4 h = make_float4(xv.x + (v.x + bb.x), xv.y + (v.y + bb.y), xv.z + (v.z + bb.z),
-                                       xv.w + (v.w + bb.w));
-          *reinterpret_cast<float4 *>(a.h1 + slot * g.d + c) = h;
-          st_bf4(a.hb + slot * g.d + c, h.x * gn.x, h.y * gn.y, h.z * gn.z, h.w * gn.w);
-          ss = h.x * h.x + h.y * h.y + h.z * h.z + h.w * h.w;
-        } else {
-          const float4 h = hr[n];
-          st_bf4(a.y + (long)rpatch[r] * g.d + c, h.x + (v.x + bb.x), h.y + (v.y + bb.y),
-                 h.z + (v.z + bb.z), h.w + (v.w + bb.w));
-        }
-      }
-      if (MODE == V_O) {
-        // 64 columns of a row are 16 consecutive lanes
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-        if (rv && cv && (lane & 15) == 0) a.ssq[(long)rslot[r] * a.parts + c / kVitSsqCols] = ss;
-      }
-    }
-  }
-}
-
-template <int MODE>
-__global__ __launch_bounds__(512) void k_vit_gemm(VitGemm a, const int32_t *__restrict__ rows) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kVitLds];
-  __shared__ int pre[kMMaxItems + 1];
-  __shared__ int rslot[128], rpatch[128], rpos[128];
-  __shared__ float rinv[128];
-  int M;
-  if (a.B == 1) {                                // one item: its rows are the packed rows
-    M = n_valid(rows, 0, a.g.Np);
-  } else {
-    if (threadIdx.x < 64) row_prefix(rows, a.B, a.g.Np, pre);
-    __syncthreads();
-    M = pre[a.B];
-  }
-  const VitTile vt = vit_tile(MODE == V_GU, M, a.cols, a.cus);
-  if ((int)blockIdx.x >= vt.tiles) return;
-  const int tm = MODE == V_GU ? kVitGuTM[vt.v] : kVitTM[vt.v];
-  const int mt = (M + tm - 1) / tm;
-  const int l = xcd_tile(blockIdx.x, vt.tiles), nt = l / mt, row0 = (l - nt * mt) * tm;
-  const int nvalid = min(tm, M - row0);
-#define FC_VT(i)                                                                               \
-  vit_gemm_tile<MODE, MODE == V_GU ? kVitGuTM[i] : kVitTM[i], MODE == V_GU ? kVitGuTN[i] : kVitTN[i]>( \
-      a, lds, pre, rslot, rpatch, rpos, rinv, row0, nvalid, nt)
-  switch (vt.v) {
-    case 0: FC_VT(0); break;
-    case 1: FC_VT(1); break;
-    case 2: FC_VT(2); break;
-    default: FC_VT(3); break;
-  }
-#undef FC_VT
-}
-
-// The most tiles any row count up to `rows` takes (the grid; surplus workgroups exit).
-int vit_grid(bool gu, int rows, int cols, int cus) {
-  int most = 1;
-  for (int r = 1; r <= rows; r += 32)
-    most = std::max(most, vit_tile(gu, std::min(r + 31, rows), cols, cus).tiles);
-  return most;
-}
-
-template <int MODE>
-fc_status run_vit_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const VitGemm &a) {
-  const int grid = vit_grid(MODE == V_GU, a.B * a.g.Np, a.cols, a.cus);
-  ProfScope ps(ctx, st, name);
-  hipLaunchKernelGGL(k_vit_gemm<MODE>, dim3((unsigned)grid), dim3(512), 0, st, a,
-                     (const int32_t *)ctx->vit_rows);
-  FC_LAUNCH_OK(st, "k_vit_gemm");
-  return FC_OK;
-}
-
 // --------------------------------------------------------------------- patch merger
 // Grid (item x recomputed token, patch): the patch row RMS-normalised, written at its
 // place in the token's concatenated row (hidden = merge^2 d).
@@ -931,9 +533,6 @@ __global__ __launch_bounds__(kVitThreads) void k_merge_norm(
   norm_row(y + (((long)b * N + t) * mm + a) * d, gain, d, eps, hb + (s * mm + a) * d, red);
 }
 
-__device__ __forceinline__ float gelu_erf(float v) {
-  return 0.5f * v * (1.f + erff(v * 0.70710678118654752f));
-}
 // Grid (slot, 1024-column chunk): split-K sums + bias, exact GELU (x Phi(x)), bf16
 template <int SPL>
 __global__ __launch_bounds__(kVitThreads) void k_merge_red_gelu(
@@ -1001,8 +600,10 @@ static fc_status vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
   const int wkeys = c.window > 0 ? std::min(c.window, g.gh) * std::min(c.window, g.gw) * g.mm : g.Np;
   uint16_t *krot = wkeys > 64 ? reinterpret_cast<uint16_t *>(ctx->part) : nullptr;
   fc_status rc;
-  VitGemm a{};
+  RowGemm a{};
   a.krot = krot;
+  a.qw = a.kw = g.d;
+  const int32_t *rows = ctx->vit_rows;
   a.B = B;
   a.cus = std::max(ctx->num_cus, 1);
   a.idx = idx;
@@ -1010,7 +611,7 @@ static fc_status vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
   a.rope = ctx->vit_rope;
   a.h1 = ctx->h1;
   a.ssq = ctx->part + slots * g.d;
-  a.parts = (g.d + kVitSsqCols - 1) / kVitSsqCols;
+  a.parts = (g.d + kRowSsqCols - 1) / kRowSsqCols;
   a.eps = L.rms_eps;
   {
     ProfScope ps(ctx, st, "fc_vit_gather_norm");
@@ -1022,7 +623,7 @@ static fc_status vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
   a.A = ctx->hb; a.W = L.w_qkv; a.bias = L.b_qkv;
   a.K = g.d; a.cols = 3 * g.d;
   a.q = ctx->qbuf; a.kc = c.k; a.vc = c.v;
-  if ((rc = run_vit_gemm<V_QKV>(ctx, st, "fc_vit_gemm_qkv", a)) != FC_OK) return rc;
+  if ((rc = run_row_gemm<V_QKV>(ctx, st, "fc_vit_gemm_qkv", a, rows)) != FC_OK) return rc;
   {
     // query chunks of 64 per window (full attention: one window of every patch)
     const int chunks = (wkeys + kVitQ - 1) / kVitQ;
@@ -1050,13 +651,13 @@ static fc_status vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
   a.A = ctx->attn; a.W = L.w_o; a.bias = L.b_o;
   a.cols = g.d;
   a.x = x; a.g2 = L.g2; a.hb = ctx->hb;
-  if ((rc = run_vit_gemm<V_O>(ctx, st, "fc_vit_gemm_o", a)) != FC_OK) return rc;
+  if ((rc = run_row_gemm<V_O>(ctx, st, "fc_vit_gemm_o", a, rows)) != FC_OK) return rc;
   a.A = ctx->hb; a.W = L.w_gate_up; a.bias = L.b_gate_up;
   a.cols = 2 * f; a.act = ctx->act;
-  if ((rc = run_vit_gemm<V_GU>(ctx, st, "fc_vit_gemm_gateup", a)) != FC_OK) return rc;
+  if ((rc = run_row_gemm<V_GU>(ctx, st, "fc_vit_gemm_gateup", a, rows)) != FC_OK) return rc;
   a.A = ctx->act; a.W = L.w_down; a.bias = L.b_down;
   a.K = f; a.cols = g.d; a.y = y;
-  return run_vit_gemm<V_DOWN>(ctx, st, "fc_vit_gemm_down", a);
+  return run_row_gemm<V_DOWN>(ctx, st, "fc_vit_gemm_down", a, rows);
 }
 
 fc_status launch_vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache &c,
@@ -1112,7 +713,6 @@ fc_status launch_vit_merger(fc_ctx *ctx, const fc_merger_desc &M, const uint16_t
   const long slots = (long)B * N;
   uint16_t *hb = ctx->act;                                   // normalised token rows
   uint16_t *act = ctx->act + slots * hidden;                 // GELU outputs
-  int splits = 1;
   fc_status rc;
   {
     ProfScope ps(ctx, st, "fc_merge_norm");
@@ -1120,6 +720,24 @@ fc_status launch_vit_merger(fc_ctx *ctx, const fc_merger_desc &M, const uint16_t
                        y, M.g, idx, nrec, N, mm, M.d_model, M.rms_eps, hb);
     FC_LAUNCH_OK(st, "k_merge_norm");
   }
+  if (row_gemm_pays(hidden, B * ((N + 255L) / 256)) && B <= kMMaxItems) {
+    RowGemm a{};
+    a.cus = std::max(ctx->num_cus, 1);
+    a.B = B;
+    a.idx = idx;
+    a.g.N = a.g.Np = N;
+    a.g.m = a.g.mm = 1;
+    a.K = hidden;
+    a.A = hb; a.W = M.w1; a.bias = M.b1;
+    a.cols = a.g.d = hidden;
+    a.act = act;
+    if ((rc = run_row_gemm<M_GELU>(ctx, st, "fc_merge_gemm1", a, nrec)) != FC_OK) return rc;
+    a.A = act; a.W = M.w2; a.bias = M.b2;
+    a.cols = a.g.d = M.d_out;
+    a.y = x_out;
+    return run_row_gemm<M_OUT>(ctx, st, "fc_merge_gemm2", a, nrec);
+  }
+  int splits = 1;
   if ((rc = run_plain_gemm(ctx, st, "fc_merge_gemm1", hb, M.w1, hidden, hidden, N, nrec,
                            ctx->part, B, &splits)) != FC_OK)
     return rc;

@@ -570,3 +570,30 @@ def test_long_cache_few_rows(fc, ctx_big, slots):
              slot_seed=91 if slots else None)
     worst = c.check(fc, ctx_big, [fcdata.random_reuse_ids(92, 1024, 84)])
     print(f"worst rel-L2 {worst:.2e}")
+
+
+def few_shape(d, heads, hd, ffn):
+    return fcdata.LayerShape(d=d, n_heads=heads, n_kv=heads, hd=hd, ffn=ffn)
+
+
+@pytest.mark.parametrize("shape,N,counts,kw", [
+    (few_shape(64, 1, 64, 64), 40, [1], {}),                       # one K step, one row
+    (few_shape(192, 3, 64, 320), 140, [129, 0, 65], {}),           # tiles cut by rows and columns
+    (GQA_SMALL, 64, [31, 1, 64], dict(gw=8, mrope=QWEN_MROPE, slot_seed=121)),
+    (few_shape(128, 2, 64, 5184), 64, [50], {}),                   # down: K dealt over the chip
+    (few_shape(128, 2, 64, 5184), 64, [50, 3, 64], {}),            # the same K, more items
+    (few_shape(64, 1, 64, 64), 1, [1] * 1024 + [0, 1], {}),        # items past one launch
+])
+def test_few_row_tiles(fc, shape, N, counts, kw):
+    """The row tiles of the projections where a tile ends at the last row or column, packs rows
+    of several items, or K is one step; both down projections; a second launch of items."""
+    B, T = len(counts), 16
+    c = Case(shape, T=T, N=N, W=1, head=0, B=B, seed=120, **kw)
+    ctx = fc.Context(fc.Caps(max_batch=B, max_height=28, max_width=28, max_tokens=N, max_seq=T + N,
+                             max_d_model=shape.d, max_ffn=shape.ffn,
+                             max_qkv=(shape.n_heads + 2 * shape.n_kv) * shape.hd))
+    rng = np.random.default_rng(122)
+    try:
+        c.check(fc, ctx, [np.sort(rng.permutation(N)[:n]) for n in counts])
+    finally:
+        ctx.close()

@@ -319,6 +319,15 @@ def test_merger_other_merge_factors(fc, ctx, m):
                                    np.arange(36, dtype=np.int32)], 375 + m)
 
 
+@pytest.mark.parametrize("counts", [[20], [9, 0, 16]])
+def test_merger_long_rows(fc, ctx, counts):
+    """Merged rows of 5760 features: one item's GEMMs deal K over the chip, three items' take
+    the row tiles."""
+    sh = fcdata.MergerShape(d=640, m=3, d_out=80)
+    rng = np.random.default_rng(380)
+    check_merger(fc, ctx, sh, 24, [np.sort(rng.permutation(24)[:n]).astype(np.int32) for n in counts], 381)
+
+
 def test_merger_qwen_shape(fc, ctx):
     """The Qwen2.5-VL merger (1280 x 4 = 5120 -> 5120 -> 3584) on a 448 x 448 frame's 256
     tokens, half of them recomputed."""
