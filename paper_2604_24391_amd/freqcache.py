@@ -9,7 +9,10 @@ The library must be built (paper_2604_24391_amd.build); there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
+import operator
 import os
+import struct
 from dataclasses import dataclass, field
 
 import torch  # imported before the library so both share torch's HIP runtime
@@ -204,9 +207,29 @@ def _ptr(t: torch.Tensor, dtype, numel: int, name: str):
         raise ValueError(f"{name} must be contiguous")
     if t.numel() < numel:
         raise ValueError(f"{name} has {t.numel()} elements, the call touches {numel}")
-    if t.data_ptr() % 16:
+    p = t.data_ptr()
+    if p % 16:
         raise ValueError(f"{name} must be 16-byte aligned")
-    return c_void_p(t.data_ptr())
+    return p
+
+
+_get_is_cuda, _get_dtype = operator.attrgetter("is_cuda"), operator.attrgetter("dtype")
+
+
+def _ptrs(ts, dtype, numels, names):
+    """_ptr of several tensors (numels, names: one each).  The checks go over the whole list in
+    C loops: a call over 28 layers checks 112 tensors, which one by one took longer than the
+    call's kernels.  A list that fails one is checked again tensor by tensor, for its error."""
+    try:
+        p = list(map(torch.Tensor.data_ptr, ts))
+        if (all(map(_get_is_cuda, ts)) and list(map(_get_dtype, ts)).count(dtype) == len(p)
+                and all(map(torch.Tensor.is_contiguous, ts))
+                and all(map(operator.ge, map(torch.Tensor.numel, ts), numels))
+                and functools.reduce(operator.or_, p, 0) % 16 == 0):
+            return p
+    except (TypeError, AttributeError, RuntimeError):   # not a list of plain tensors
+        pass
+    return [_ptr(t, dtype, n, name) for t, n, name in zip(ts, numels, names)]
 
 
 # ------------------------------------------------------------------------------ context
@@ -467,8 +490,7 @@ class LayerDesc:
         w = self.weights
         sizes = dict(w_qkv=q * d, b_qkv=q, w_o=d * o, w_gate=f * d, w_up=f * d, w_down=d * f,
                      g_attn=d, g_mlp=d)
-        ptrs = [_ptr(w[n], torch.bfloat16, sizes[n], n) for n in
-                ("w_qkv", "b_qkv", "w_o", "w_gate", "w_up", "w_down", "g_attn", "g_mlp")]
+        ptrs = _ptrs([w[n] for n in sizes], torch.bfloat16, sizes.values(), sizes)
         return fc_layer_desc(d, self.n_heads, self.n_kv_heads, self.head_dim, f, self.rms_eps,
                              self.rope_theta, *ptrs)
 
@@ -505,7 +527,7 @@ class KVCache:
                            self.text_tokens, self.frame_tokens, self.window, self.head,
                            self.grid_w, (c_int32 * 3)(*self.mrope), self.trail_tokens,
                            _ptr(self.slot_map, torch.int32, B * self.S, "slot_map")
-                           if self.slot_map is not None else c_void_p(0))
+                           if self.slot_map is not None else 0)
 
     def logical(self, t: torch.Tensor, B: int) -> torch.Tensor:
         """k or v in row order: rows gathered through the slot map (t itself without one)."""
@@ -513,6 +535,36 @@ class KVCache:
             return t
         m = self.slot_map[:B * self.S].view(B, self.S).long()
         return torch.stack([t[b].index_select(0, m[b]) for b in range(B)])
+
+
+_KV_STRUCT = struct.Struct("@PP9iP")          # fc_kv_cache
+_kv_layout = operator.attrgetter("text_tokens", "frame_tokens", "window", "head", "grid_w",
+                                 "trail_tokens", "mrope")
+_kv_slot_map, _kv_k, _kv_v = (operator.attrgetter(n) for n in ("slot_map", "k", "v"))
+
+
+def _kv_array(kvs, B: int, kvw: int):
+    """fc_kv_cache[len(kvs)].  The layers of a model share everything but their k and v: then the
+    rest is laid out once and k and v are checked together."""
+    n = len(kvs)
+    first, smap = kvs[0], kvs[0].slot_map
+    try:
+        lay = _kv_layout(first)
+        shared = all(s is smap for s in map(_kv_slot_map, kvs)) and \
+            list(map(_kv_layout, kvs)).count(lay) == n
+        T, N, W, head, gw, trail, mrope = lay
+        a, b, c = mrope
+        pm = 0 if smap is None else _ptr(smap, torch.int32, B * first.S, "slot_map")
+        rest = _KV_STRUCT.pack(0, 0, T, N, W, head, gw, a, b, c, trail, pm)[16:]
+    except (TypeError, ValueError, struct.error):
+        shared = False
+    if not shared or _KV_STRUCT.size != ctypes.sizeof(fc_kv_cache):
+        return (fc_kv_cache * n)(*[kv.c(B, kvw) for kv in kvs])
+    size = (B * first.S * kvw,) * n
+    kp = _ptrs(list(map(_kv_k, kvs)), torch.bfloat16, size, ("k",) * n)
+    vp = _ptrs(list(map(_kv_v, kvs)), torch.bfloat16, size, ("v",) * n)
+    pair = struct.Struct("@PP").pack
+    return (fc_kv_cache * n).from_buffer_copy(b"".join([pair(k, v) + rest for k, v in zip(kp, vp)]))
 
 
 def fc_layer_forward(ctx: Context, layer: LayerDesc, kv: KVCache, x_cur: torch.Tensor,
@@ -598,12 +650,13 @@ def fc_cache_update_layers(ctx: Context, layer: LayerDesc, kvs, y_prevs, y_curs,
     N, d = kvs[0].frame_tokens, layer.d_model
     kvw = layer.n_kv_heads * layer.head_dim
     cl = layer.c()
-    cks = (fc_kv_cache * n)(*[kv.c(B, kvw) for kv in kvs])
+    cks = _kv_array(kvs, B, kvw)
     if y_prevs is None:
         yp = yc = None
     else:
-        yp = (c_void_p * n)(*[_ptr(y, torch.bfloat16, B * N * d, "y_prev") for y in y_prevs])
-        yc = (c_void_p * n)(*[_ptr(y, torch.bfloat16, B * N * d, "y_cur") for y in y_curs])
+        size = (B * N * d,) * n
+        yp = (c_void_p * n)(*_ptrs(y_prevs, torch.bfloat16, size, ("y_prev",) * n))
+        yc = (c_void_p * n)(*_ptrs(y_curs, torch.bfloat16, size, ("y_cur",) * n))
     _check(lib().fc_cache_update_layers(
         ctx.handle, ctypes.byref(cl), n, cks, yp, yc,
         _ptr(shift, torch.int32, 2 * B, "shift"),
@@ -626,7 +679,7 @@ class VitDesc:
         d, f = self.d_model, self.d_ffn
         sizes = dict(w_qkv=3 * d * d, b_qkv=3 * d, w_o=d * d, b_o=d, w_gate_up=2 * f * d,
                      b_gate_up=2 * f, w_down=d * f, b_down=d, g1=d, g2=d)
-        ptrs = [_ptr(self.w[k], torch.bfloat16, n, k) for k, n in sizes.items()]
+        ptrs = _ptrs([self.w[k] for k in sizes], torch.bfloat16, sizes.values(), sizes)
         return fc_vit_desc(d, self.n_heads, self.head_dim, f, self.rms_eps, self.rope_theta, *ptrs)
 
 
@@ -698,7 +751,7 @@ class MergerDesc:
     def c(self) -> fc_merger_desc:
         h = self.merge * self.merge * self.d_model
         sizes = dict(g=self.d_model, w1=h * h, b1=h, w2=self.d_out * h, b2=self.d_out)
-        ptrs = [_ptr(self.w[k], torch.bfloat16, n, k) for k, n in sizes.items()]
+        ptrs = _ptrs([self.w[k] for k in sizes], torch.bfloat16, sizes.values(), sizes)
         return fc_merger_desc(self.d_model, self.merge, self.d_out, self.rms_eps, *ptrs)
 
 

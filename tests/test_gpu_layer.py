@@ -597,3 +597,29 @@ def test_few_row_tiles(fc, shape, N, counts, kw):
         c.check(fc, ctx, [np.sort(rng.permutation(N)[:n]) for n in counts])
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["shared", "slots", "mixed"])
+def test_layer_lists_marshal_like_single_layers(fc, kind):
+    """Caches of several layers as one array: byte for byte what each layer's own descriptor
+    holds (layouts that differ included, for the library to refuse); a tensor of the list that
+    fails a check raises that check's error."""
+    from paper_2604_24391_amd import freqcache as F
+    B, T, N, W, kvw = 2, 16, 12, 3, 64
+    S = T + N * W + 4
+    mk = lambda: torch.zeros(B, S, 1, kvw, dtype=torch.bfloat16, device="cuda")
+    smap = fc.slot_state_alloc(B, S) if kind == "slots" else None
+    kvs = [fc.KVCache(mk(), mk(), T, N, W, head=1 if kind == "mixed" and i == 1 else 2, grid_w=4,
+                      mrope=(8, 8, 16), trail_tokens=4, slot_map=smap) for i in range(3)]
+    got, want = F._kv_array(kvs, B, kvw), [kv.c(B, kvw) for kv in kvs]
+    for g, w in zip(got, want):
+        for name, _ in F.fc_kv_cache._fields_:
+            a, b = getattr(g, name), getattr(w, name)
+            assert (list(a) == list(b)) if name == "mrope_section" else a == b, name
+    flat = torch.zeros(B * S * kvw + 8, dtype=torch.bfloat16, device="cuda")
+    for bad, msg in ((None, "required"), (mk().cpu(), "GPU"), (mk().float(), "bfloat16"),
+                     (mk().transpose(0, 1), "contiguous"), (mk()[:1], "elements"),
+                     (flat[1:], "aligned")):
+        kvs[1].v = bad
+        with pytest.raises(ValueError, match=msg):
+            F._kv_array(kvs, B, kvw)
