@@ -251,8 +251,8 @@ def main():
     el2 = time.perf_counter() - t2
     fc.fc_profile_enable(ctx, False)
     for name in ("fc_spectra", "fc_grid", "fc_patchsim", "fc_topk", "fc_cache_update", "fc_gather_norm",
-                 "fc_gemm_qkv", "fc_red_qkv", "fc_attn", "fc_attn_combine", "fc_gemm_o",
-                 "fc_red_o", "fc_gemm_gateup", "fc_gemm_down", "fc_red_down"):
+                 "fc_gemm_qkv", "fc_attn", "fc_attn_combine", "fc_gemm_o", "fc_gemm_gateup",
+                 "fc_gemm_down", "fc_red_down"):
         tot, cnt = fc.fc_profile_read(ctx, name)
         if cnt:
             kern[name] = dict(avg_us=round(tot * 1e3 / cnt, 3), launches=cnt,
@@ -722,9 +722,8 @@ def bench_vit(fc, torch):
     torch.cuda.synchronize()
     fc.fc_profile_enable(ctx, False)
     kern = {}
-    for name in ("fc_vit_gather_norm", "fc_vit_gemm_qkv", "fc_vit_red_qkv", "fc_vit_attn",
-                 "fc_vit_gemm_o", "fc_vit_red_o", "fc_vit_gemm_gateup", "fc_vit_red_gu",
-                 "fc_vit_gemm_down", "fc_vit_red_down"):
+    for name in ("fc_vit_gather_norm", "fc_vit_gemm_qkv", "fc_vit_attn", "fc_vit_gemm_o",
+                 "fc_vit_gemm_gateup", "fc_vit_gemm_down"):
         tot, cnt = fc.fc_profile_read(ctx, name)
         kern[name] = round(tot * 1e3 / max(cnt, 1), 2)
     fc.fc_profile_read(ctx, None, reset=True)
@@ -758,8 +757,7 @@ def bench_vit(fc, torch):
     torch.cuda.synchronize()
     fc.fc_profile_enable(ctx, False)
     mkern = {}
-    for name in ("fc_merge_norm", "fc_merge_gemm1", "fc_merge_red_gelu", "fc_merge_gemm2",
-                 "fc_merge_red_out"):
+    for name in ("fc_merge_norm", "fc_merge_gemm1", "fc_merge_gemm2"):
         tot, cnt = fc.fc_profile_read(ctx, name)
         mkern[name] = round(tot * 1e3 / max(cnt, 1), 2)
     fc.fc_profile_read(ctx, None, reset=True)
