@@ -713,6 +713,9 @@ fc_status launch_vit_merger(fc_ctx *ctx, const fc_merger_desc &M, const uint16_t
   const long slots = (long)B * N;
   uint16_t *hb = ctx->act;                                   // normalised token rows
   uint16_t *act = ctx->act + slots * hidden;                 // GELU outputs
+  // (the row tiles need no partial sums; what fits does not depend on the GEMM taken)
+  if ((size_t)slots * std::max(hidden, M.d_out) > ctx->part_elems)
+    return fail(FC_ERR_CAPACITY, "fc_vit_merger_forward: partial sums exceed the workspace");
   fc_status rc;
   {
     ProfScope ps(ctx, st, "fc_merge_norm");
