@@ -94,10 +94,10 @@ __device__ __forceinline__ float gelu_erf(float v) {
 // and its reductions).  The DMA pattern alone takes 7.3 us for QKV (37 B a clock and CU); LDS
 // traffic (operands written once and read twice), about 3 us before the first step is staged
 // and 2 us of epilogue make up the rest.  Decoder layer (d 3584, 162 rows), against the
-// weight-streaming GEMM with its K parts and their reductions: QKV 24 + 10 -> 20 (5 of them
-// the norm's launch before it: 25), O 23 + 7 -> 20; the toy layer (d 256) 59 -> 40 in all.  The
-// merger (hidden 5120, 162 rows) 45 + 11 -> 55 with its weights from memory, 40 when they are
-// in the memory-side cache.
+// weight-streaming GEMM with its K parts and their reductions: QKV 24 + 10 -> 20 (and 5 for
+// the rows' norm, which that GEMM did itself), O 23 + 7 -> 20; the toy layer (d 256) 59 -> 40
+// in all.  The merger (hidden 5120, 162 rows) 45 + 11 -> 55 with its weights from memory, 40
+// when they are in the memory-side cache.
 enum { V_QKV, V_O, V_GU, V_DOWN, L_QKV, L_O, L_DOWN, M_GELU, M_OUT };
 constexpr int kRowLds = 150 * 1024;
 constexpr int kRowSsqCols = 64;         // columns per partial sum of squares of h1
