@@ -140,10 +140,10 @@ __global__ __launch_bounds__(kVitThreads) void k_vit_gather_norm(
   const int t = threadIdx.x;
   const int b = (int)(s / g.Np), j = (int)(s - (long)b * g.Np);
   const int half = g.hd / 2, quarter = g.hd / 4;
-  const int e = (int)s * kVitThreads + t;
+  const long e = s * kVitThreads + t;      // past 2^31 for the last of many items' slots
   const int npos = max(g.gh, g.gw) * g.m;
   if (e < npos * 32) {
-    const int ps = e / 32, fk = e - ps * 32;
+    const int ps = (int)e / 32, fk = (int)e - ps * 32;
     if (fk < quarter) {
       const double ang = (double)ps * pow(theta, -2.0 * fk / (double)half);
       rope[e] = make_float2((float)cos(ang), (float)sin(ang));

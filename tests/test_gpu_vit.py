@@ -431,3 +431,40 @@ def test_gemm_tiles_and_key_blocks(fc, ctx, shape, gh, gw, m, window, counts):
     rng = np.random.default_rng(701)
     ids = [np.sort(rng.permutation(gh * gw)[:n]).astype(np.int32) for n in counts]
     c.check(fc, ctx, ids)
+
+
+def test_block_over_2_to_the_31_threads(fc):
+    """513 items of 16384 patches: the gather kernel's thread numbers pass 2^31 in the last item.
+    Every item holds the same frame and the first and the last recompute the same token, so
+    their rows are the same bytes as those of a call over one item; nothing else is written."""
+    d, gh, gw, m, B = 64, 32, 32, 4, 513
+    N, Np = gh * gw, gh * gw * m * m
+    assert B * Np * 256 > 2**31
+    gen = torch.Generator("cuda").manual_seed(800)
+
+    def bf(*s, std=1.0):
+        return (torch.randn(*s, device="cuda", generator=gen) * std).to(torch.bfloat16)
+    w = dict(w_qkv=bf(3 * d, d, std=.1), b_qkv=bf(3 * d), w_o=bf(d, d, std=.1), b_o=bf(d),
+             w_gate_up=bf(2 * d, d, std=.1), b_gate_up=bf(2 * d), w_down=bf(d, d, std=.1),
+             b_down=bf(d), g1=bf(d), g2=bf(d))
+    desc = fc.VitDesc(d, 1, d, d, w)
+    frame = [bf(1, Np, d) for _ in range(4)]                   # x, k, v, y of one item
+    idx = torch.full((B, N), 1000, dtype=torch.int32, device="cuda")
+    nrec = torch.zeros(B, dtype=torch.int32, device="cuda")
+    nrec[0] = nrec[-1] = 1
+
+    def run(items):
+        ctx = fc.Context(fc.Caps(max_batch=items, max_height=28, max_width=28, max_tokens=N,
+                                 max_seq=N, max_d_model=2048, max_ffn=1024, max_qkv=3072))
+        x, k, v, y = (t.repeat(items, 1, 1) for t in frame)
+        cache = fc.VitCache(k.view(items, Np, 1, d), v.view(items, Np, 1, d), gh, gw, m, 0)
+        fc.fc_vit_block_forward(ctx, desc, cache, x, idx, nrec, y)
+        torch.cuda.synchronize()
+        ctx.close()
+        return k, v, y
+    one, many = run(1), run(B)
+    rows = slice(1000 * m * m, 1001 * m * m)
+    for a, b, f in zip(one, many, frame[1:]):
+        assert not torch.equal(a[0, rows], f[0, rows])
+        assert torch.equal(b[0], a[0]) and torch.equal(b[-1], a[0])
+        assert all(torch.equal(b[i], f[0]) for i in range(1, B - 1))
