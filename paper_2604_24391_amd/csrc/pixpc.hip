@@ -21,10 +21,14 @@
 //                  and packed into one sequence, inverse FFT, real part / (H W) = the
 //                  response surface (written only when the caller asks for it) and each
 //                  row's first maximum.
-//   k_pc_peak      one workgroup per pair: first maximum over the rows (row-major ties
-//                  to the lower index), signed wrap, parabolic refinement with circular
-//                  neighbours (four values of the surface, summed from its row spectra),
-//                  the token shift.
+//   k_pc_peak      one workgroup per pair: first maximum over the rows, signed wrap,
+//                  parabolic refinement with circular neighbours (four values of the
+//                  surface, summed from its row spectra), the token shift.
+//
+// The maximum is the first element, in row order, that reaches it up to kPcTie: frames that
+// repeat along an axis (bands, tiles, a wall of one colour) have a surface of equal maxima,
+// and the rounding of a packed row's two halves and of the twiddle products would pick one
+// of them at random, up to half a frame away.
 //
 // The FFTs are of length n = 7 2^k, one sequence (several short ones) inside one wave, so
 // that their stages need no workgroup barrier: 448 points (896 for n = 896), 7 or 8 (14 or
@@ -42,7 +46,7 @@
 //   k_pc_rows 421 -> 109 us (4.7 TB/s; a large copy reaches 4.6 TB/s), k_pc_cols_fwd
 //   305 -> 61 us (5.0 TB/s), k_pc_cols_inv 129 -> 48 us (4.3 TB/s), k_pc_rows_inv
 //   249 -> 41 us (2.5 TB/s; it no longer writes the surface for the selection),
-//   k_pc_peak 4.8 -> 7.7 us (it sums the neighbours itself); fc_select 1225 -> 364 us.
+//   k_pc_peak 4.8 -> 7.7 us (it sums the neighbours itself); fc_select 1225 -> 360 us.
 //
 // Half-spectra lie in strips of 8 columns, [strip][row][8] (the last strip as wide as what
 // is left), so that a row's pieces and a strip's rows are whole 128-B lines; the cross power
@@ -68,6 +72,10 @@ namespace {
 constexpr int kPcThreads = 256;
 constexpr int kPcMaxN = 896;
 constexpr int kPcWaves = kPcThreads / 64;
+// Elements of a surface this close to its maximum, relative to it, are equal to it: the
+// rounding of the transforms is of some 1e-15, and 2e5 elements without a period leave
+// their two largest about 1e-2 apart.
+constexpr double kPcTie = 1e-12;
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -664,31 +672,32 @@ __global__ __launch_bounds__(kPcThreads) void k_pc_rows_inv(int H, int B, PixWs 
       const int yo = 2 * (g * F::S + sq);
       if (yo >= H) break;
       double best[2] = {-INFINITY, -INFINITY};
-      int arg[2] = {0x7fffffff, 0x7fffffff};
       double *row = resp ? resp + ((size_t)b * H + yo) * W : nullptr;
-      for (int x = lane; x < W; x += 64) {   // ascending x per lane: the first maximum
+      for (int x = lane; x < W; x += 64) {
         const double2 r = buf[sq * W + x];
         if (row) {
           row[x] = r.x;
           row[W + x] = r.y;
         }
-        if (r.x > best[0]) { best[0] = r.x; arg[0] = x; }
-        if (r.y > best[1]) { best[1] = r.y; arg[1] = x; }
+        if (r.x > best[0]) best[0] = r.x;
+        if (r.y > best[1]) best[1] = r.y;
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        for (int o = 32; o > 0; o >>= 1) {
-          const double v2 = __shfl_xor(best[h], o);
-          const int i2 = __shfl_xor(arg[h], o);
-          if (v2 > best[h] || (v2 == best[h] && i2 < arg[h])) {
-            best[h] = v2;
-            arg[h] = i2;
-          }
-        }
+      for (int h = 0; h < 2; ++h)
+        for (int o = 32; o > 0; o >>= 1) best[h] = fmax(best[h], __shfl_xor(best[h], o));
+      // the first element of each row that reaches its maximum (a row of NaN: element 0)
+      const double least[2] = {best[0] - kPcTie * fabs(best[0]), best[1] - kPcTie * fabs(best[1])};
+      int arg[2] = {-1, -1};
+      for (int x0 = 0; x0 < W && (arg[0] < 0 || arg[1] < 0); x0 += 64) {
+        const bool in = x0 + lane < W;
+        const double2 r = buf[sq * W + (in ? x0 + lane : 0)];
+        const unsigned long long m0 = __ballot(in && r.x >= least[0]), m1 = __ballot(in && r.y >= least[1]);
+        if (arg[0] < 0 && m0) arg[0] = x0 + __ffsll(m0) - 1;
+        if (arg[1] < 0 && m1) arg[1] = x0 + __ffsll(m1) - 1;
       }
       if (lane < 2) {
         ws.rowmax[(size_t)b * H + yo + lane] = lane ? best[1] : best[0];
-        ws.rowarg[(size_t)b * H + yo + lane] = lane ? arg[1] : arg[0];
+        ws.rowarg[(size_t)b * H + yo + lane] = max(lane ? arg[1] : arg[0], 0);
       }
     }
     wave_sync();
@@ -716,42 +725,27 @@ __global__ __launch_bounds__(kPcThreads) void k_pc_peak(int H, int W, PixWs ws,
                                                         int32_t *__restrict__ tok_shift, int tp,
                                                         int zero_shift) {
   __shared__ double bv[kPcWaves];
-  __shared__ long bi[kPcWaves];
+  __shared__ int by[kPcWaves];
   __shared__ double part[kPcWaves][4];
   const int b = blockIdx.x, t = threadIdx.x;
-  double best = -INFINITY;
-  long arg = 0x7fffffffffffffffL;
-  for (int y = t; y < H; y += blockDim.x) {
-    const double v = ws.rowmax[(size_t)b * H + y];
-    const long i = (long)y * W + ws.rowarg[(size_t)b * H + y];
-    if (v > best || (v == best && i < arg)) {
-      best = v;
-      arg = i;
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    const double v2 = __shfl_xor(best, o);
-    const long i2 = __shfl_xor(arg, o);
-    if (v2 > best || (v2 == best && i2 < arg)) {
-      best = v2;
-      arg = i2;
-    }
-  }
-  if ((t & 63) == 0) {
-    bv[t >> 6] = best;
-    bi[t >> 6] = arg;
-  }
+  const double *rowmax = ws.rowmax + (size_t)b * H;
+  double v = -INFINITY;
+  for (int y = t; y < H; y += blockDim.x) v = fmax(v, rowmax[y]);
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+  if ((t & 63) == 0) bv[t >> 6] = v;
   __syncthreads();
-  double v = bv[0];
-  long a = bi[0];
-  for (int i = 1; i < kPcWaves; ++i)
-    if (bv[i] > v || (bv[i] == v && bi[i] < a)) {
-      v = bv[i];
-      a = bi[i];
-    }
-  // a surface of NaN has no maximum: the first element stands for it
-  if (a < 0 || a >= (long)H * W) a = 0;
-  const int ki = (int)(a / W), kj = (int)(a - (long)ki * W);
+  for (int i = 0; i < kPcWaves; ++i) v = fmax(v, bv[i]);
+  // the first row that reaches it, and that row's first element (a surface of NaN: element 0)
+  const double least = v - kPcTie * fabs(v);
+  int ki = H;
+  for (int y = t; y < H; y += blockDim.x)
+    if (rowmax[y] >= least) ki = min(ki, y);
+  for (int o = 32; o > 0; o >>= 1) ki = min(ki, __shfl_xor(ki, o));
+  if ((t & 63) == 0) by[t >> 6] = ki;
+  __syncthreads();
+  for (int i = 0; i < kPcWaves; ++i) ki = min(ki, by[i]);
+  if (ki >= H) ki = 0;
+  const int kj = ws.rowarg[(size_t)b * H + ki];
   const int hw = W / 2 + 1;
   const double2 *G = ws.sa + (size_t)b * H * hw;
   const int yu = (ki - 1 + H) % H, yd = (ki + 1) % H;

@@ -94,6 +94,27 @@ def test_every_transform_length_both_ways(fc, H, W):
     np.testing.assert_array_equal(sp, sp2.cpu().numpy())
 
 
+@pytest.mark.parametrize("axis", [2, 3])
+@pytest.mark.parametrize("H,W,period", [(224, 224, 1), (448, 448, 1), (448, 448, 2), (448, 448, 7),
+                                        (448, 448, 14), (448, 448, 56), (448, 224, 2),
+                                        (224, 448, 7), (448, 224, 7), (896, 112, 2)])
+def test_frames_that_repeat_along_an_axis(fc, H, W, period, axis):
+    """Bands (period 1) and tiles of random content have a surface of equal maxima: the first of
+    them in row order is the peak, as in the oracle, whatever the rounding of the others."""
+    rng = np.random.default_rng(H * 7 + W + 100 * period + axis)
+    B = 8
+    tile = rng.random((B, 3, period, W) if axis == 2 else (B, 3, H, period)).astype(np.float32)
+    reps = (1, 1, H // period, 1) if axis == 2 else (1, 1, 1, W // period)
+    prev = np.tile(tile, reps)
+    cur = np.roll(prev, 5, axis=5 - axis).copy()
+    ctx = ctx_for(fc, B, H, W)
+    try:
+        sp, pk, rs = run_pc(fc, ctx, prev, cur)
+    finally:
+        ctx.close()
+    compare_pc(prev, cur, sp, pk, rs)
+
+
 def test_trajectory_pairs_and_missing_previous(fc):
     """Consecutive 448 x 448 frames of the benchmark trajectory, and batches without a
     previous frame or with an all-black one (shift 0, zero surface, as in the oracle)."""
