@@ -433,6 +433,41 @@ def test_gemm_tiles_and_key_blocks(fc, ctx, shape, gh, gw, m, window, counts):
     c.check(fc, ctx, ids)
 
 
+def test_silu_keeps_float32_precision(fc, ctx):
+    """A block whose MLP hands SiLU(gate bias) (up bias) to its output unchanged (x and every
+    other weight zero, the down projection the identity), for every bf16 gate of magnitude
+    2^-6 to 80 beside random up values: the bf16 result is the rounding of a value within 6 ulp
+    of float32 of the exact one (exp 1 ulp, sum, quotient and product half an ulp each, and
+    the exponent's own rounding none, since a gate is a short number)."""
+    d = 2048
+    z = torch.zeros
+    w = dict(w_qkv=z(3 * d, d), b_qkv=z(3 * d), w_o=z(d, d), b_o=z(d), w_gate_up=z(2 * d, d),
+             w_down=torch.eye(d), b_down=z(d), g1=torch.ones(d), g2=torch.ones(d))
+    w = {k: v.to(torch.bfloat16).cuda() for k, v in w.items()}
+    mag = torch.arange(0x3C80, 0x42A0, dtype=torch.int16).view(torch.bfloat16)
+    gates = torch.cat([mag, -mag])
+    gen = torch.Generator().manual_seed(810)
+    bad = total = 0
+    for _ in range(16):
+        pick = torch.randint(len(gates), (d,), generator=gen)
+        pick[:d // 2] = torch.randint(len(gates) - 512, len(gates), (d // 2,), generator=gen)
+        gate, up = gates[pick], (1 + torch.rand(d, generator=gen)).to(torch.bfloat16)
+        w["b_gate_up"] = torch.cat([gate, up]).cuda()
+        kv = [z(1, 1, 16, 128, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        y = z(1, 1, d, dtype=torch.bfloat16, device="cuda")
+        one = torch.ones(1, dtype=torch.int32, device="cuda")
+        fc.fc_vit_block_forward(ctx, fc.VitDesc(d, 16, 128, d, w), fc.VitCache(*kv, 1, 1, 1, 0),
+                                torch.zeros_like(y), torch.zeros_like(one), one, y)
+        g64 = gate.double()
+        s = g64 / (1 + torch.exp(-g64)) * up.double()
+        lo, hi = ((s * (1 + e * 6 * 2.0**-24)).to(torch.bfloat16) for e in (-1, 1))
+        got = y[0, 0].cpu()
+        bad += int(((got != lo) & (got != hi)).sum())
+        total += d
+    print(f"{bad} of {total} outside")
+    assert bad == 0
+
+
 def test_block_over_2_to_the_31_threads(fc):
     """513 items of 16384 patches: the gather kernel's thread numbers pass 2^31 in the last item.
     Every item holds the same frame and the first and the last recompute the same token, so
