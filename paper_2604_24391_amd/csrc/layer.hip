@@ -4,9 +4,9 @@
 // token of batch item b, j < n_recompute[b] (read on the device, so no host
 // sync); grids are sized for N rows per item and surplus tiles exit.
 //
-//   k_gather_norm  the recomputed tokens' rows of x by id, RMS-normalised, as the QKV
-//               GEMM's bf16 operand.
-//   k_row_gemm  QKV (bias, rotated q stored, raw k and v scattered into the current frame's
+//   k_gather_norm  the recomputed tokens' rows of x by id times the RMSNorm gain, as the QKV
+//               GEMM's bf16 operand, and their 1/rms (k_mgemm's rows: normalised).
+//   k_row_gemm  QKV (1/rms, bias, rotated q stored, raw k and v scattered into the current frame's
 //               cache rows), O (residual -> h1 in float32, the SwiGLU operand
 //               bf16(h1 * g_mlp) and sums of squares of h1) and short down projections
 //               (residual, output rows scattered): row tiles over the slots, whole K range.
@@ -372,12 +372,15 @@ __device__ float block_sum256(float v, float *red) {
 }
 
 // One workgroup per slot: the gathered token's row of x, normalised and scaled by the
-// attention RMSNorm gain, as the QKV GEMM's bf16 operand.
+// attention RMSNorm gain, as the QKV GEMM's bf16 operand.  With inv_out the row is scaled by
+// the gain alone and its 1/rms written there, for the GEMM's epilogue: x g is exact where the
+// gain is a short number, and 1/rms then never rounds to bf16.
 __global__ __launch_bounds__(256) void k_gather_norm(const uint16_t *__restrict__ x,
                                                      const uint16_t *__restrict__ gain,
                                                      const int32_t *__restrict__ idx,
                                                      const int32_t *__restrict__ nrec, int N,
-                                                     int d, float eps, uint16_t *__restrict__ xs) {
+                                                     int d, float eps, uint16_t *__restrict__ xs,
+                                                     float *__restrict__ inv_out) {
   __shared__ float red[256];
   const long slot = blockIdx.x;
   const int b = (int)(slot / N), j = (int)(slot - (long)b * N);
@@ -402,6 +405,8 @@ __global__ __launch_bounds__(256) void k_gather_norm(const uint16_t *__restrict_
   }
   ss = block_sum256(ss, red);
   const float inv = 1.f / sqrtf(ss / (float)d + eps);
+  if (inv_out && threadIdx.x == 0) inv_out[slot] = inv;
+  const float mul = inv_out ? 1.f : inv;
 #pragma unroll
   for (int it = 0; it < kIt; ++it) {
     const int c = (it * 256 + threadIdx.x) * 8;
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(256) void k_gather_norm(const uint16_t *__restrict_
       const U16x8 g = *reinterpret_cast<const U16x8 *>(gain + c);
       U16x8 o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o.v[e] = f2bf(bf2f(v[it].v[e]) * inv * bf2f(g.v[e]));
+      for (int e = 0; e < 8; ++e) o.v[e] = f2bf(bf2f(v[it].v[e]) * mul * bf2f(g.v[e]));
       *reinterpret_cast<U16x8 *>(xs + slot * d + c) = o;
     }
   }
@@ -1680,6 +1685,7 @@ fc_status run_layer_rows(fc_ctx *ctx, hipStream_t st, const char *name, RowGemm 
     if (a.idx) a.idx += n;
     if (rows) rows += kMMaxItems;
     if (MODE == L_QKV) {
+      a.rinv += n;
       a.q += n * a.qw;
       a.kc += (long)kMMaxItems * a.S * a.kw;
       a.vc += (long)kMMaxItems * a.S * a.kw;
@@ -1764,18 +1770,19 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
   p.mr = mr;
   p.x = x_cur; p.g2 = L.g_mlp;
   p.h1 = ctx->h1; p.hb = ctx->hb; p.y = y_cur;
+  p.rinv = ctx->ssq;
   // sums of squares per 64 columns, beside no partial sums that are in use at the time
   p.ssq = ctx->part;
   p.parts = d / kRowSsqCols;
 
-  // 1. QKV of the recomputed rows: gather + RMSNorm of the rows, then a GEMM whose
-  //    epilogue adds the bias, rotates q and scatters raw k, v into the current frame's
-  //    cache rows
+  // 1. QKV of the recomputed rows: gather + RMSNorm of the rows (few rows: 1/rms apart), then
+  //    a GEMM whose epilogue (scales by 1/rms,) adds the bias, rotates q and scatters raw k, v
+  //    into the current frame's cache rows
   {
     {
       ProfScope ps(ctx, st, "fc_gather_norm");
       hipLaunchKernelGGL(k_gather_norm, dim3((unsigned)rows), dim3(256), 0, st, x_cur, L.g_attn,
-                         idx, nrec, N, d, L.rms_eps, ctx->hb);
+                         idx, nrec, N, d, L.rms_eps, ctx->hb, big ? nullptr : ctx->ssq);
       FC_LAUNCH_OK(st, "k_gather_norm");
     }
     if (big) {

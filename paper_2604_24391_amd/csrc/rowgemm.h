@@ -77,8 +77,8 @@ __device__ __forceinline__ float gelu_erf(float v) {
 //     multiplying, with or without the halves of the workgroup in alternating phases, was up
 //     to 30 % slower: the DMAs keep the MFMAs waiting.)
 //   * The accumulators go through LDS as whole rows, so that every global access of the
-//     epilogue is a piece of a row: the QKV modes add the bias, rotate q and scatter raw k and
-//     v into the cache; the O modes add the residual (V_O: and the bias) and write h1, the MLP
+//     epilogue is a piece of a row: the QKV modes (L_QKV: times 1/rms) add the bias, rotate q
+//     and scatter raw k and v into the cache; the O modes add the residual (V_O: and the bias) and write h1, the MLP
 //     operand bf16(h1 g2) and the row's sums of squares per 64 columns; V_GU applies 1/rms,
 //     adds the biases and writes SiLU(g) u; the DOWN modes add h1 (V_DOWN: and the bias) and
 //     scatter the output rows; M_GELU adds the bias and writes GELU; M_OUT adds the bias and
@@ -114,6 +114,7 @@ struct RowGemm {
   int qw, kw;                           // QKV: columns of q and of k (and v)
   uint16_t *q, *kc, *vc, *krot;         // QKV (krot: V_QKV)
   const int32_t *smap;                  // L_QKV: slot map of the cache rows
+  const float *rinv;                    // L_QKV: 1/rms of each slot's row
   int S, cur_row0, qpos0;               // L_QKV: cache rows, the region's first row and position
   MRope mr;                             // L_QKV
   const uint16_t *x, *g2;               // O
@@ -223,7 +224,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
     lds_barrier();                                         // barrier nk: the stages are free
   } else {
     // -------------------------------------------------------------------- MFMA waves
-    // the tile's rows: slot, patch row (b Np + patch) and, for V_GU, 1/rms of h1
+    // the tile's rows: slot, patch row (b Np + patch) and 1/rms of x (L_QKV) or h1 (V_GU)
     if (t < TM) {
       int b = 0;
       const long sl = row_slot(pre, a.B, g.Np, row0 + min(t, nvalid - 1), b);
@@ -242,6 +243,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
         if (MODE == L_QKV) {
           rpatch[t] = b * a.S + pool_row(a.smap, b, a.S, a.cur_row0 + tok);   // cache row
           rpos[t] = a.qpos0 + tok;
+          rinv[t] = a.rinv[sl];
         } else {
           rpatch[t] = b * g.N + tok;
         }
@@ -349,8 +351,8 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
         float y0[4], y1[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          x0[i] = v4[i] + bb0[i];
-          x1[i] = u4[i] + bb1[i];
+          x0[i] = MODE == L_QKV ? fmaf(v4[i], rinv[r], bb0[i]) : v4[i] + bb0[i];
+          x1[i] = MODE == L_QKV ? fmaf(u4[i], rinv[r], bb1[i]) : u4[i] + bb1[i];
           if (rot) {
             y0[i] = x0[i] * cs[n][i].x - x1[i] * cs[n][i].y;
             y1[i] = x1[i] * cs[n][i].x + x0[i] * cs[n][i].y;

@@ -599,6 +599,31 @@ def test_few_row_tiles(fc, shape, N, counts, kw):
         ctx.close()
 
 
+def test_few_row_qkv_operand_is_exact_for_short_gains(fc, ctx):
+    """With a power-of-two attention gain the products x g are bf16 numbers, so new K and V rows
+    are the rounding of a float32 sum: as far from the 64-bit values as the rounding of those
+    alone, up to the sum's own error (1e-6 of a row here, against roundings of 1.6e-3; a
+    second rounding of the operand would be 1.4 times as far)."""
+    sh, N, T = GQA_SMALL, 64, 16
+    wt = dict(fcdata.layer_weights(130, sh))
+    rng = np.random.default_rng(131)
+    wt["g_attn"] = fcdata.bf16_round(rng.choice([0.5, 1.0, 2.0], sh.d).astype(np.float32))
+    c = Case(sh, T=T, N=N, W=1, head=0, B=1, seed=130, wt=wt)
+    ids = np.sort(rng.permutation(N)[:40])
+    _, k, v = c.run(fc, ctx, [ids])
+    f64 = lambda a: fcdata.bf16_to_f32(a).astype(np.float64)
+    x = f64(c.x_cur[0][ids])
+    h = x * f64(wt["g_attn"]) / np.sqrt((x * x).mean(1, keepdims=True) + 1e-6)
+    want = h @ f64(wt["w_qkv"]).T + f64(wt["b_qkv"])
+    kw = sh.n_kv * sh.hd
+    for got, w in ((k, want[:, -2 * kw:-kw]), (v, want[:, -kw:])):
+        got = f64(got[0][c.lay.cur_rows(ids)].reshape(len(ids), kw))
+        rnd = np.linalg.norm(f64(fcdata.bf16_round(w.astype(np.float32))) - w)
+        err = np.linalg.norm(got - w)
+        print(f"error {err / np.linalg.norm(w):.3e}, of rounding alone {rnd / np.linalg.norm(w):.3e}")
+        assert err <= 1.02 * rnd
+
+
 @pytest.mark.parametrize("kind", ["shared", "slots", "mixed"])
 def test_layer_lists_marshal_like_single_layers(fc, kind):
     """Caches of several layers as one array: byte for byte what each layer's own descriptor
