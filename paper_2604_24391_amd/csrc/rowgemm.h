@@ -58,6 +58,11 @@ __device__ __forceinline__ void st_bf4(uint16_t *p, float a, float b, float c, f
   *reinterpret_cast<uint2 *>(p) = make_uint2(f2bf(a) | ((uint32_t)f2bf(b) << 16),
                                              f2bf(c) | ((uint32_t)f2bf(d) << 16));
 }
+// Rotary pair (a, b) turned by (cos, sin) = cs, with the same two roundings wherever it is done:
+// a cached key and one just written then have the same rotated bits.
+__device__ __forceinline__ float2 rot_pair(float a, float b, float2 cs) {
+  return make_float2(fmaf(a, cs.x, -(b * cs.y)), fmaf(b, cs.x, a * cs.y));
+}
 __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (1.f + erff(v * 0.70710678118654752f));
 }
@@ -354,8 +359,12 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
           x0[i] = MODE == L_QKV ? fmaf(v4[i], rinv[r], bb0[i]) : v4[i] + bb0[i];
           x1[i] = MODE == L_QKV ? fmaf(u4[i], rinv[r], bb1[i]) : u4[i] + bb1[i];
           if (rot) {
-            y0[i] = x0[i] * cs[n][i].x - x1[i] * cs[n][i].y;
-            y1[i] = x1[i] * cs[n][i].x + x0[i] * cs[n][i].y;
+            // a key is rotated as the cache holds it, rounded: the step that computes it and
+            // those that reuse it attend to the same bits
+            const float2 y = isq ? rot_pair(x0[i], x1[i], cs[n][i])
+                                 : rot_pair(bf2f(f2bf(x0[i])), bf2f(f2bf(x1[i])), cs[n][i]);
+            y0[i] = y.x;
+            y1[i] = y.y;
           }
         }
         if (!isq) {

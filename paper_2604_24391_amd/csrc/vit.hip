@@ -164,10 +164,10 @@ __global__ __launch_bounds__(kVitThreads) void k_vit_gather_norm(
       const int h = p / half, c = h * g.hd + (p - h * half);
       const float4 x0 = bf4(kr + c), x1 = bf4(kr + c + half);
       const float2 *w = cs + (p - h * half);
-      st_bf4(krot + s * g.d + c, x0.x * w[0].x - x1.x * w[0].y, x0.y * w[1].x - x1.y * w[1].y,
-             x0.z * w[2].x - x1.z * w[2].y, x0.w * w[3].x - x1.w * w[3].y);
-      st_bf4(krot + s * g.d + c + half, x1.x * w[0].x + x0.x * w[0].y, x1.y * w[1].x + x0.y * w[1].y,
-             x1.z * w[2].x + x0.z * w[2].y, x1.w * w[3].x + x0.w * w[3].y);
+      const float2 y0 = rot_pair(x0.x, x1.x, w[0]), y1 = rot_pair(x0.y, x1.y, w[1]),
+                   y2 = rot_pair(x0.z, x1.z, w[2]), y3 = rot_pair(x0.w, x1.w, w[3]);
+      st_bf4(krot + s * g.d + c, y0.x, y1.x, y2.x, y3.x);
+      st_bf4(krot + s * g.d + c + half, y0.y, y1.y, y2.y, y3.y);
     }
   }
   if (j == 0 && t == 0) rows_out[b] = n_rows(nrec, g, b);
@@ -348,8 +348,9 @@ __global__ __launch_bounds__(512) void k_vit_attn(
           const int pair = kc0[i] + q2;
           const bool lo = pair < quarter;
           const float2 cs = rope[(lo ? pr : pc) * 32 + (lo ? pair : pair - quarter)];
-          rx[q2] = x * cs.x - y * cs.y;
-          ry[q2] = y * cs.x + x * cs.y;
+          const float2 z = rot_pair(x, y, cs);
+          rx[q2] = z.x;
+          ry[q2] = z.y;
         }
         st_bf8(dst, rx);
         st_bf8(dst + half, ry);

@@ -433,6 +433,32 @@ def test_gemm_tiles_and_key_blocks(fc, ctx, shape, gh, gw, m, window, counts):
     c.check(fc, ctx, ids)
 
 
+@pytest.mark.parametrize("window,hd", [(0, 80), (0, 64), (6, 80), (4, 80), (0, 112)])
+def test_recomputed_and_reused_keys_attend_alike(fc, ctx, window, hd):
+    """A step that recomputes every token, then one that recomputes some of them from the same
+    input and reuses the others' keys and values: the same bytes, whichever route rotates the
+    keys (windows of at most 64 keys rotate them on load)."""
+    sh = fcdata.VitShape(d=4 * hd, heads=4, hd=hd, ffn=448)
+    gh, gw, m, np_ = 8, 9, 2, 288
+    desc = gpu_desc(fc, fcdata.vit_weights(820, sh), sh)
+    gen = torch.Generator("cuda").manual_seed(821)
+    x, y = (torch.randn(1, np_, sh.d, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.zeros(1, np_, 4, hd, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    cache = fc.VitCache(k, v, gh, gw, m, window)
+
+    def run(ids):
+        idx = torch.zeros(1, gh * gw, dtype=torch.int32)
+        idx[0, :len(ids)] = torch.from_numpy(ids)
+        fc.fc_vit_block_forward(ctx, desc, cache, x, idx.cuda(),
+                                torch.tensor([len(ids)], dtype=torch.int32, device="cuda"), y)
+        return [t.clone() for t in (k, v, y)]
+    whole = run(np.arange(gh * gw, dtype=np.int32))
+    for reuse in (30, 80):
+        ids = np.sort(fcdata.random_reuse_ids(822 + reuse, gh * gw, reuse)).astype(np.int32)
+        for a, b in zip(run(ids), whole):
+            assert torch.equal(a, b)
+
+
 def test_silu_keeps_float32_precision(fc, ctx):
     """A block whose MLP hands SiLU(gate bias) (up bias) to its output unchanged (x and every
     other weight zero, the down projection the identity), for every bf16 gate of magnitude
