@@ -757,9 +757,11 @@ def bench_vit(fc, torch):
     torch.cuda.synchronize()
     fc.fc_profile_enable(ctx, False)
     mkern = {}
-    for name in ("fc_merge_norm", "fc_merge_gemm1", "fc_merge_gemm2"):
+    for name in ("fc_merge_norm", "fc_merge_gemm1", "fc_merge_red_gelu", "fc_merge_gemm2",
+                 "fc_merge_red_out"):
         tot, cnt = fc.fc_profile_read(ctx, name)
-        mkern[name] = round(tot * 1e3 / max(cnt, 1), 2)
+        if cnt:
+            mkern[name] = round(tot * 1e3 / cnt, 2)
     fc.fc_profile_read(ctx, None, reset=True)
     # the encoder of the deployed model: 32 blocks, full attention in 4 of them
     enc = {f"reuse{r}": round((28 * out["window4"][f"reuse{r}"]["graph_us"]

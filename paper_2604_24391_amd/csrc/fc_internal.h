@@ -199,12 +199,19 @@ __device__ __forceinline__ int pool_row(const int32_t *map, int b, int S, int r)
   return p < 0 ? 0 : (p >= S ? S - 1 : p);
 }
 
-// Split-K partial sums of A[B N][K] W[Nout][K]^T over the first nrec[b] rows of each
-// item, no epilogue; K a multiple of 64, Nout of 16: the weight-streaming GEMM,
-// part = C[split][B N][Nout], *splits = its split count.
-fc_status run_plain_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const uint16_t *A,
-                         const uint16_t *W, int K, int Nout, int N, const int32_t *nrec,
-                         float *part, int B, int *splits);
+// One projection of the patch merger over the first nrec[b] rows of each item (layer.hip):
+// A[B N][K] W[Nout][K]^T + bias, GELU of it to out[B N][Nout] or (gelu false) the rows scattered
+// to out[B][N][Nout] by token id.  red.splits 0: done.  Otherwise the split-K partial sums lie in
+// ctx->part, C[split][B N][Nout], and a reduction has to add them up, add the bias and write the
+// rows, unless (red.need > 0) the items' rows take red.need streams of the weights or more.
+// K a multiple of 64, Nout of 16.
+struct MergerRed {
+  int splits = 0, need = 0;
+};
+fc_status run_merger_gemm(fc_ctx *ctx, hipStream_t st, const char *name, bool gelu,
+                          const uint16_t *A, const uint16_t *W, const uint16_t *bias, int K,
+                          int Nout, int N, const int32_t *idx, const int32_t *nrec, uint16_t *out,
+                          int B, MergerRed &red);
 
 // Vision-encoder block with partial recompute and its cache update (vit.hip).
 // Reused tokens' K/V rows (and output rows, when y_prev is given) copied from a previous

@@ -186,6 +186,7 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
         }
       }
     };
+    loads_done();
     for (int u = 0; u < PD - 1 && u < nk; ++u) issue(u, u);
     for (int k = 0; k < nk; ++k) {
       wait_vm_rt(min(nk - 1 - k, PD - 2) * L);                 // this wave's share of step k
@@ -290,9 +291,7 @@ __device__ __forceinline__ void wgemm_tile(const WArgs &a, unsigned char *lds, f
 }
 
 template <int MODE>
-__global__ __launch_bounds__(512) void k_wgemm(WArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
-  __shared__ __attribute__((aligned(16))) float rowinv[MT];   // SwiGLU: 1/rms per row
+__device__ __forceinline__ void wgemm(const WArgs &a, unsigned char *lds, float *rowinv) {
   // split fastest: with 8 splits every split's workgroups share one XCD and its L2
   const int bid = blockIdx.x;
   const int sp = bid % a.splits;
@@ -312,10 +311,31 @@ __global__ __launch_bounds__(512) void k_wgemm(WArgs a) {
   }
 }
 
+template <int MODE>
+__global__ __launch_bounds__(512) void k_wgemm(WArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
+  __shared__ __attribute__((aligned(16))) float rowinv[MT];   // SwiGLU: 1/rms per row
+  wgemm<MODE>(a, lds, rowinv);
+}
+
+// Row tiles with the epilogue of mode RM, or the weight-streaming GEMM's partial sums (to be
+// reduced by a kernel that exits in the other case), decided by the rows there are: `need`
+// streams of the weights or more take the row tiles.  One launch, surplus workgroups exit.
+template <int RM>
+__global__ __launch_bounds__(512) void k_row_or_stream(RowGemm a, WArgs w, int need) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
+  static_assert(kRowLds % 16 == 0 && kRowLds + sizeof(RowLds) <= kLdsBytes, "the row tables fit");
+  if (weight_streams(w.nrec, a.B, a.g.Np) >= need)
+    row_gemm<RM>(a, w.nrec, lds, *reinterpret_cast<RowLds *>(lds + kRowLds));
+  else if ((int)blockIdx.x < a.B * w.tpb * w.ncg * w.splits)
+    wgemm<G_DOWN>(w, lds, nullptr);
+}
+
 // ------------------------------------------------------------------------------- reductions
 // One workgroup per (row, 1024-column chunk); each thread sums the split-K partials of
 // 4 columns with float4 loads and applies the epilogue of its projection.
 struct RedArgs {
+  int need, B;                    // k_red_down: exit from `need` streams on (0: never)
   int N, d, splits, ncols, qw, kw, S, cur_row0;
   int hd, qpos0;                  // head dim; prompt position of current-frame token 0
   const float2 *rope;             // [S][hd/2] (cos, sin)
@@ -425,6 +445,7 @@ __global__ __launch_bounds__(256) void k_red_down(RedArgs r) {
   const long slot = blockIdx.x;
   const int b = (int)(slot / r.N), j = (int)(slot - (long)b * r.N);
   if (j >= n_valid(r.nrec, b, r.N)) return;
+  if (r.need && weight_streams(r.nrec, r.B, r.N) >= r.need) return;
   const int c = blockIdx.y * 1024 + threadIdx.x * 4;
   if (c >= r.d) return;
   const int tok = tok_of(r.idx, slot, r.N);
@@ -1585,7 +1606,7 @@ __global__ __launch_bounds__(256) void k_cache_update_layers(CacheLayers m) {
 // at most NBLK blocks per group, and enough (group, split) pairs to cover the CUs
 // about once; every split keeps at least 4 K steps and the partial sums fit.
 template <int MODE>
-fc_status run_wgemm(fc_ctx *ctx, hipStream_t st, const char *name, WArgs &g, int B) {
+fc_status plan_wgemm(fc_ctx *ctx, const char *name, WArgs &g, int B, long &total) {
   if (g.K % KS || g.Nout % 16)
     return fail(FC_ERR_SHAPE, "%s: K %d must be a multiple of %d and N %d of 16", name, g.K, KS, g.Nout);
   const int cus = std::max(ctx->num_cus, 1);
@@ -1606,10 +1627,31 @@ fc_status run_wgemm(fc_ctx *ctx, hipStream_t st, const char *name, WArgs &g, int
   g.splits = (ksteps + g.ksteps - 1) / g.ksteps;
   if (MODE != G_GU && (size_t)g.splits * g.rows * g.Nout > ctx->part_elems)
     return fail(FC_ERR_CAPACITY, "%s: partial sums exceed the workspace", name);
-  const long total = (long)B * g.tpb * g.ncg * g.splits;
+  total = (long)B * g.tpb * g.ncg * g.splits;
+  return FC_OK;
+}
+
+template <int MODE>
+fc_status run_wgemm(fc_ctx *ctx, hipStream_t st, const char *name, WArgs &g, int B) {
+  long total;
+  const fc_status rc = plan_wgemm<MODE>(ctx, name, g, B, total);
+  if (rc != FC_OK) return rc;
   ProfScope ps(ctx, st, name);
   hipLaunchKernelGGL(k_wgemm<MODE>, dim3((unsigned)total), dim3(512), 0, st, g);
   FC_LAUNCH_OK(st, "k_wgemm");
+  return FC_OK;
+}
+
+template <int RM>
+fc_status run_row_or_stream(fc_ctx *ctx, hipStream_t st, const char *name, const RowGemm &a, WArgs &g) {
+  long total;
+  const fc_status rc = plan_wgemm<G_DOWN>(ctx, name, g, a.B, total);
+  if (rc != FC_OK) return rc;
+  total = std::max<long>(total, row_grid(false, a.B * a.g.Np, a.cols, a.cus));
+  ProfScope ps(ctx, st, name);
+  hipLaunchKernelGGL(k_row_or_stream<RM>, dim3((unsigned)total), dim3(512), 0, st, a, g,
+                     row_streams(a.K));
+  FC_LAUNCH_OK(st, "k_row_or_stream");
   return FC_OK;
 }
 
@@ -1926,16 +1968,23 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
     g.A = ctx->act; g.W0 = L.w_down;
     g.K = ffn; g.Nout = d; g.N = N; g.r = r;
     if ((rc = run_mgemm<G_DOWN>(ctx, st, "fc_mgemm_down", g, B)) != FC_OK) return rc;
-  } else if (row_gemm_pays(ffn, B * ((N + MT - 1L) / MT))) {
+  } else {
+    const Route route = row_route(ffn, B, N, nrec);
     p.A = ctx->act; p.W = L.w_down;
     p.K = ffn; p.cols = d;
-    if ((rc = run_layer_rows<L_DOWN>(ctx, st, "fc_gemm_down", p, B, nrec)) != FC_OK) return rc;
-  } else {
+    if (route == kRowTiles) return run_layer_rows<L_DOWN>(ctx, st, "fc_gemm_down", p, B, nrec);
     WArgs g{};
     g.A = ctx->act; g.W0 = L.w_down;
     g.K = ffn; g.Nout = d; g.N = N; g.nrec = nrec;
     g.part = ctx->part; g.rows = rows;
-    if ((rc = run_wgemm<G_DOWN>(ctx, st, "fc_gemm_down", g, B)) != FC_OK) return rc;
+    if (route == kOnDevice) {
+      p.B = r.B = B;
+      r.need = row_streams(ffn);
+      rc = run_row_or_stream<L_DOWN>(ctx, st, "fc_gemm_down", p, g);
+    } else {
+      rc = run_wgemm<G_DOWN>(ctx, st, "fc_gemm_down", g, B);
+    }
+    if (rc != FC_OK) return rc;
     r.splits = g.splits; r.ncols = d;
     ProfScope ps(ctx, st, "fc_red_down");
     run_red_down(dim3((unsigned)rows, (d + 1023) / 1024), st, r);
@@ -1944,15 +1993,36 @@ fc_status launch_layer(fc_ctx *ctx, const fc_layer_desc &L, const fc_kv_cache &k
   return FC_OK;
 }
 
-fc_status run_plain_gemm(fc_ctx *ctx, hipStream_t st, const char *name, const uint16_t *A,
-                         const uint16_t *W, int K, int Nout, int N, const int32_t *nrec,
-                         float *part, int B, int *splits) {
+fc_status run_merger_gemm(fc_ctx *ctx, hipStream_t st, const char *name, bool gelu,
+                          const uint16_t *A, const uint16_t *W, const uint16_t *bias, int K,
+                          int Nout, int N, const int32_t *idx, const int32_t *nrec, uint16_t *out,
+                          int B, MergerRed &red) {
+  RowGemm a{};
+  a.cus = std::max(ctx->num_cus, 1);
+  a.B = B;
+  a.idx = idx;
+  a.g.N = a.g.Np = N;
+  a.g.m = a.g.mm = 1;
+  a.A = A; a.W = W; a.bias = bias;
+  a.K = K;
+  a.cols = a.g.d = Nout;
+  a.act = a.y = out;
+  // the packed row map of a row GEMM holds kMMaxItems items
+  const Route route = B <= kMMaxItems ? row_route(K, B, N, nrec) : kStream;
+  red = MergerRed{};
+  if (route == kRowTiles)
+    return gelu ? run_row_gemm<M_GELU>(ctx, st, name, a, nrec) : run_row_gemm<M_OUT>(ctx, st, name, a, nrec);
   WArgs g{};
   g.A = A; g.W0 = W;
   g.K = K; g.Nout = Nout; g.N = N; g.nrec = nrec;
-  g.part = part; g.rows = (long)B * N;
-  fc_status rc = run_wgemm<G_DOWN>(ctx, st, name, g, B);
-  *splits = g.splits;
+  g.part = ctx->part; g.rows = (long)B * N;
+  fc_status rc;
+  if (route == kOnDevice)
+    rc = gelu ? run_row_or_stream<M_GELU>(ctx, st, name, a, g) : run_row_or_stream<M_OUT>(ctx, st, name, a, g);
+  else
+    rc = run_wgemm<G_DOWN>(ctx, st, name, g, B);
+  red.splits = g.splits;
+  red.need = route == kOnDevice ? row_streams(K) : 0;
   return rc;
 }
 

@@ -101,8 +101,7 @@ __device__ __forceinline__ float gelu_erf(float v) {
 // and 2 us of epilogue make up the rest.  Decoder layer (d 3584, 162 rows), against the
 // weight-streaming GEMM with its K parts and their reductions: QKV 24 + 10 -> 20 (and 5 for
 // the rows' norm, which that GEMM did itself), O 23 + 7 -> 20; the toy layer (d 256) 59 -> 40
-// in all.  The merger (hidden 5120, 162 rows) 45 + 11 -> 55 with its weights from memory, 40
-// when they are in the memory-side cache.
+// in all.  Where K is long and the rows few the weight-streaming GEMM is faster: row_streams.
 enum { V_QKV, V_O, V_GU, V_DOWN, L_QKV, L_O, L_DOWN, M_GELU, M_OUT };
 constexpr int kRowLds = 150 * 1024;
 constexpr int kRowSsqCols = 64;         // columns per partial sum of squares of h1
@@ -131,12 +130,37 @@ struct RowGemm {
   float eps;
 };
 
-// Whether a projection over K is faster here than in the weight-streaming GEMM, which deals
-// K over the chip (and needs a reduction of its partial sums) but streams the weights once per
-// 256 rows of an item.  mtiles: those streams.  Measured, us here against there, down
-// projection (3584 columns), weights from memory: 162 rows K 4864 24.7 / 24.2, K 9728 44 / 32,
-// K 18944 79 / 48; 4 items of 162 rows 44 / 80, 84 / 114, 153 / 175.
-constexpr bool row_gemm_pays(int K, long mtiles) { return K <= 80 * KS || mtiles >= 3; }
+// Streams of the weights (one per 256 recomputed rows of an item, and one for the rest) from
+// which a projection over K is faster here than in the weight-streaming GEMM, which deals K over
+// the chip and reduces its partial sums.  Measured with weights from memory, 3584 columns, a
+// whole layer, here / there in us:
+//   1 stream, 162 / 256 rows: K 4096 129 / 136, 156 / 165; K 4864 133 / 139, 162 / 168; K 6144
+//     140 / 139, 170 / 171; K 9728 155 / 137, 187 / 176; K 18944 200 / 162, 237 / 191; 26 rows:
+//     K 2048 94 / 95, K 4864 105 / 98, K 6144 110 / 99
+//   2 streams, one item of 300 / 512 rows: K 7168 235 / 239, 282 / 297; K 9728 257 / 243,
+//     304 / 310; K 18944 341 / 291, 381 / 348; two items of 162: K 7168 224 / 232, K 9728 242 / 240
+//   3 streams, one item of 600 / three of 162 rows: K 9728 373 / 390, 320 / 335; K 12288
+//     407 / 405, 348 / 354; K 18944 482 / 459, 415 / 409; one item of 655: K 18944 471 / 481
+//   4 streams, one item of 1024 / four of 162 rows: K 18944 630 / 660, 494 / 527
+// and the merger (K 5120 twice): 26 / 128 / 256 rows 55 / 39, 57 / 54, 75 / 68; two items of 162
+// 78 / 96; one of 400 86 / 103.
+constexpr int row_streams(int K) { return K < 5120 ? 1 : K < 9216 ? 2 : 3; }
+// Which of the two a call takes.  Every item has at least one recomputed row as a rule, so the
+// number of items decides alone where it reaches row_streams (an item without rows then costs
+// time, not its result).  Where the slots could hold that many streams but the items need not,
+// the rows decide, on the device (nrec null: every slot is a row).
+enum Route { kStream, kRowTiles, kOnDevice };
+inline Route row_route(int K, int B, int N, const int32_t *nrec) {
+  const int need = row_streams(K);
+  if (B >= need) return kRowTiles;
+  if (B * ((N + 255L) / 256) < need) return kStream;
+  return nrec ? kOnDevice : kRowTiles;
+}
+__device__ __forceinline__ int weight_streams(const int32_t *nrec, int B, int N) {
+  int n = 0;
+  for (int b = 0; b < B; ++b) n += (n_valid(nrec, b, N) + 255) >> 8;
+  return n;
+}
 
 struct RowTile {
   int v, tiles;                         // variant, tiles of all rows
@@ -219,6 +243,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
 #pragma unroll
       for (int i = 0; i < L; ++i) dma16(gp[i] + k * KS, st + i * 4096);
     };
+    loads_done();
     for (int k = 0; k < NST - 1 && k < nk; ++k) issue(k);
     for (int k = 0; k < nk; ++k) {
       if (k + NST - 1 <= nk) wait_vm<(NST - 2) * L>();     // this wave's share of step k
@@ -429,19 +454,23 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
   }
 }
 
+// What a workgroup knows of its tile's rows, beside the stages in LDS.
+struct RowLds {
+  int pre[kMMaxItems + 4];
+  int slot[128], patch[128], pos[128];
+  float inv[128];
+};
+
 template <int MODE>
-__global__ __launch_bounds__(512) void k_row_gemm(RowGemm a, const int32_t *__restrict__ rows) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kRowLds];
-  __shared__ int pre[kMMaxItems + 1];
-  __shared__ int rslot[128], rpatch[128], rpos[128];
-  __shared__ float rinv[128];
+__device__ __forceinline__ void row_gemm(const RowGemm &a, const int32_t *rows, unsigned char *lds,
+                                         RowLds &s) {
   int M;
   if (a.B == 1) {                                // one item: its rows are the packed rows
     M = n_valid(rows, 0, a.g.Np);
   } else {
-    if (threadIdx.x < 64) row_prefix(rows, a.B, a.g.Np, pre);
+    if (threadIdx.x < 64) row_prefix(rows, a.B, a.g.Np, s.pre);
     __syncthreads();
-    M = pre[a.B];
+    M = s.pre[a.B];
   }
   const RowTile vt = row_tile(MODE == V_GU, M, a.cols, a.cus);
   if ((int)blockIdx.x >= vt.tiles) return;
@@ -451,7 +480,7 @@ __global__ __launch_bounds__(512) void k_row_gemm(RowGemm a, const int32_t *__re
   const int nvalid = min(tm, M - row0);
 #define FC_VT(i)                                                                               \
   row_gemm_tile<MODE, MODE == V_GU ? kRowGuTM[i] : kRowTM[i], MODE == V_GU ? kRowGuTN[i] : kRowTN[i]>( \
-      a, lds, pre, rslot, rpatch, rpos, rinv, row0, nvalid, nt)
+      a, lds, s.pre, s.slot, s.patch, s.pos, s.inv, row0, nvalid, nt)
   switch (vt.v) {
     case 0: FC_VT(0); break;
     case 1: FC_VT(1); break;
@@ -459,6 +488,13 @@ __global__ __launch_bounds__(512) void k_row_gemm(RowGemm a, const int32_t *__re
     default: FC_VT(3); break;
   }
 #undef FC_VT
+}
+
+template <int MODE>
+__global__ __launch_bounds__(512) void k_row_gemm(RowGemm a, const int32_t *__restrict__ rows) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kRowLds];
+  __shared__ RowLds s;
+  row_gemm<MODE>(a, rows, lds, s);
 }
 
 // The most tiles any row count up to `rows` takes (the grid; surplus workgroups exit).

@@ -537,11 +537,12 @@ __global__ __launch_bounds__(kVitThreads) void k_merge_norm(
 // Grid (slot, 1024-column chunk): split-K sums + bias, exact GELU (x Phi(x)), bf16
 template <int SPL>
 __global__ __launch_bounds__(kVitThreads) void k_merge_red_gelu(
-    const float *__restrict__ part, int splits, const uint16_t *__restrict__ bias,
+    const float *__restrict__ part, int splits, int need, int B, const uint16_t *__restrict__ bias,
     const int32_t *__restrict__ nrec, int N, int hidden, uint16_t *__restrict__ act) {
   const long s = blockIdx.x;
   const int b = (int)(s / N), j = (int)(s - (long)b * N);
   if (j >= min(max(nrec[b], 0), N)) return;
+  if (need && weight_streams(nrec, B, N) >= need) return;
   const int c = 4 * (blockIdx.y * kVitThreads + threadIdx.x);
   if (c >= hidden) return;
   const float4 v = sum_parts4<SPL>(part, splits, (long)gridDim.x, s, hidden, c);
@@ -553,12 +554,13 @@ __global__ __launch_bounds__(kVitThreads) void k_merge_red_gelu(
 // Grid (slot, 1024-column chunk): split-K sums + bias into the token's output row
 template <int SPL>
 __global__ __launch_bounds__(kVitThreads) void k_merge_red_out(
-    const float *__restrict__ part, int splits, const uint16_t *__restrict__ bias,
+    const float *__restrict__ part, int splits, int need, int B, const uint16_t *__restrict__ bias,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ nrec, int N, int d_out,
     uint16_t *__restrict__ x_out) {
   const long s = blockIdx.x;
   const int b = (int)(s / N), j = (int)(s - (long)b * N);
   if (j >= min(max(nrec[b], 0), N)) return;
+  if (need && weight_streams(nrec, B, N) >= need) return;
   const int c = 4 * (blockIdx.y * kVitThreads + threadIdx.x);
   if (c >= d_out) return;
   const int t = min(max(idx[s], 0), N - 1);
@@ -570,7 +572,7 @@ __global__ __launch_bounds__(kVitThreads) void k_merge_red_out(
 }  // namespace
 
 // A reduction kernel instantiated for the smallest power of two >= the split count
-#define FC_VIT_RED(kern, grid, ...)                                                     \
+#define FC_VIT_RED(kern, grid, splits, ...)                                             \
   do {                                                                                  \
     if (splits <= 1) hipLaunchKernelGGL(kern<1>, grid, dim3(kVitThreads), 0, st, __VA_ARGS__);      \
     else if (splits <= 2) hipLaunchKernelGGL(kern<2>, grid, dim3(kVitThreads), 0, st, __VA_ARGS__); \
@@ -724,42 +726,25 @@ fc_status launch_vit_merger(fc_ctx *ctx, const fc_merger_desc &M, const uint16_t
                        y, M.g, idx, nrec, N, mm, M.d_model, M.rms_eps, hb);
     FC_LAUNCH_OK(st, "k_merge_norm");
   }
-  if (row_gemm_pays(hidden, B * ((N + 255L) / 256)) && B <= kMMaxItems) {
-    RowGemm a{};
-    a.cus = std::max(ctx->num_cus, 1);
-    a.B = B;
-    a.idx = idx;
-    a.g.N = a.g.Np = N;
-    a.g.m = a.g.mm = 1;
-    a.K = hidden;
-    a.A = hb; a.W = M.w1; a.bias = M.b1;
-    a.cols = a.g.d = hidden;
-    a.act = act;
-    if ((rc = run_row_gemm<M_GELU>(ctx, st, "fc_merge_gemm1", a, nrec)) != FC_OK) return rc;
-    a.A = act; a.W = M.w2; a.bias = M.b2;
-    a.cols = a.g.d = M.d_out;
-    a.y = x_out;
-    return run_row_gemm<M_OUT>(ctx, st, "fc_merge_gemm2", a, nrec);
-  }
-  int splits = 1;
-  if ((rc = run_plain_gemm(ctx, st, "fc_merge_gemm1", hb, M.w1, hidden, hidden, N, nrec,
-                           ctx->part, B, &splits)) != FC_OK)
+  MergerRed red;
+  if ((rc = run_merger_gemm(ctx, st, "fc_merge_gemm1", true, hb, M.w1, M.b1, hidden, hidden, N, idx,
+                            nrec, act, B, red)) != FC_OK)
     return rc;
-  {
+  if (red.splits) {
     ProfScope ps(ctx, st, "fc_merge_red_gelu");
     const dim3 grid((unsigned)slots, (unsigned)((hidden + 1023) / 1024));
-    FC_VIT_RED(k_merge_red_gelu, grid, (const float *)ctx->part, splits, M.b1, nrec, N, hidden,
-               act);
+    FC_VIT_RED(k_merge_red_gelu, grid, red.splits, (const float *)ctx->part, red.splits, red.need, B,
+               M.b1, nrec, N, hidden, act);
     FC_LAUNCH_OK(st, "k_merge_red_gelu");
   }
-  if ((rc = run_plain_gemm(ctx, st, "fc_merge_gemm2", act, M.w2, hidden, M.d_out, N, nrec,
-                           ctx->part, B, &splits)) != FC_OK)
+  if ((rc = run_merger_gemm(ctx, st, "fc_merge_gemm2", false, act, M.w2, M.b2, hidden, M.d_out, N, idx,
+                            nrec, x_out, B, red)) != FC_OK)
     return rc;
-  {
+  if (red.splits) {
     ProfScope ps(ctx, st, "fc_merge_red_out");
     const dim3 grid((unsigned)slots, (unsigned)((M.d_out + 1023) / 1024));
-    FC_VIT_RED(k_merge_red_out, grid, (const float *)ctx->part, splits, M.b2, idx, nrec, N,
-               M.d_out, x_out);
+    FC_VIT_RED(k_merge_red_out, grid, red.splits, (const float *)ctx->part, red.splits, red.need, B,
+               M.b2, idx, nrec, N, M.d_out, x_out);
     FC_LAUNCH_OK(st, "k_merge_red_out");
   }
   return FC_OK;

@@ -582,6 +582,12 @@ def few_shape(d, heads, hd, ffn):
     (GQA_SMALL, 64, [31, 1, 64], dict(gw=8, mrope=QWEN_MROPE, slot_seed=121)),
     (few_shape(128, 2, 64, 5184), 64, [50], {}),                   # down: K dealt over the chip
     (few_shape(128, 2, 64, 5184), 64, [50, 3, 64], {}),            # the same K, more items
+    # the down projection's kernel chosen on the device: one item of 512 (K dealt over the chip)
+    # or more rows than that (row tiles), two items of two or of three 256-row streams
+    (few_shape(128, 2, 64, 9280), 700, [512], {}),
+    (few_shape(128, 2, 64, 9280), 700, [513], {}),
+    (few_shape(128, 2, 64, 9280), 300, [300, 0], {}),
+    (few_shape(128, 2, 64, 9280), 300, [1, 257], {}),
     (few_shape(64, 1, 64, 64), 1, [1] * 1024 + [0, 1], {}),        # items past one launch
 ])
 def test_few_row_tiles(fc, shape, N, counts, kw):

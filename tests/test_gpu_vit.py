@@ -319,13 +319,38 @@ def test_merger_other_merge_factors(fc, ctx, m):
                                    np.arange(36, dtype=np.int32)], 375 + m)
 
 
-@pytest.mark.parametrize("counts", [[20], [9, 0, 16]])
-def test_merger_long_rows(fc, ctx, counts):
+@pytest.mark.parametrize("n_tokens,counts", [(24, [20]), (24, [9, 0, 16]), (300, [256]), (300, [257])])
+def test_merger_long_rows(fc, ctx, n_tokens, counts):
     """Merged rows of 5760 features: one item's GEMMs deal K over the chip, three items' take
-    the row tiles."""
+    the row tiles, as does one item of more than 256 rows."""
     sh = fcdata.MergerShape(d=640, m=3, d_out=80)
     rng = np.random.default_rng(380)
-    check_merger(fc, ctx, sh, 24, [np.sort(rng.permutation(24)[:n]).astype(np.int32) for n in counts], 381)
+    check_merger(fc, ctx, sh, n_tokens,
+                 [np.sort(rng.permutation(n_tokens)[:n]).astype(np.int32) for n in counts], 381)
+
+
+@pytest.mark.parametrize("n", [0, 100, 256, 257, 400])
+def test_merger_kernel_follows_the_rows(fc, ctx, n):
+    """One item of long merged rows: what decides between the row tiles and K dealt over the
+    chip is the recomputed rows, not the slots.  Up to 256 rows of 520 slots give the bytes of
+    a call with 256 slots, more of them the bytes of two items (always row tiles)."""
+    sh = fcdata.MergerShape(d=640, m=3, d_out=80)
+    desc = merger_desc(fc, fcdata.merger_weights(383, sh), sh)
+    gen = torch.Generator("cuda").manual_seed(384)
+    y = torch.randn(1, 520 * 9, sh.d, device="cuda", generator=gen).to(torch.bfloat16)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+
+    def run(slots, items):
+        idx = torch.zeros(items, slots, dtype=torch.int32, device="cuda")
+        idx[0, :n] = ids
+        nrec = torch.full((items,), 1, dtype=torch.int32, device="cuda")
+        nrec[0] = n
+        x = torch.zeros(items, slots, sh.d_out, dtype=torch.bfloat16, device="cuda")
+        fc.fc_vit_merger_forward(ctx, desc, y[:, :slots * 9].repeat(items, 1, 1), idx, nrec, x)
+        torch.cuda.synchronize()
+        assert not x[0, n:].any()
+        return x[0, :n]
+    assert torch.equal(run(520, 1), run(256, 1) if n <= 256 else run(520, 2))
 
 
 def test_merger_qwen_shape(fc, ctx):
