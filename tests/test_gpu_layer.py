@@ -605,6 +605,43 @@ def test_few_row_tiles(fc, shape, N, counts, kw):
         ctx.close()
 
 
+@pytest.mark.parametrize("ffn", [64, 5184])
+@pytest.mark.parametrize("slots", [False, True])
+def test_items_past_one_launch(fc, slots, ffn):
+    """1030 items of 3 tokens and 2 trailing rows, each with its own ids, counts and slot map:
+    recompute and trailing text give the bytes of two calls over 515 items (one launch each)."""
+    B, T, N, W, U, sh = 1030, 4, 3, 2, 2, few_shape(64, 1, 64, ffn)
+    S = T + W * N + U
+    desc = fcutil.layer_desc(sh, fcutil.weights_gpu(fcdata.layer_weights(140, sh)))
+    gen = torch.Generator("cuda").manual_seed(141)
+    bf = lambda *shp: torch.randn(*shp, device="cuda", generator=gen).to(torch.bfloat16)
+    k0, v0, x, y0, xt = bf(B, S, 1, 64), bf(B, S, 1, 64), bf(B, N, 64), bf(B, N, 64), bf(B, U, 64)
+    idx = torch.rand(B, N, device="cuda", generator=gen).argsort(1).to(torch.int32)
+    nrec = torch.randint(0, N + 1, (B,), device="cuda", generator=gen, dtype=torch.int32)
+    idx = torch.where(torch.arange(N, device="cuda") < nrec[:, None], idx, 9).sort(1).values.contiguous()
+    smap = torch.arange(S, dtype=torch.int32, device="cuda").repeat(B, 1)
+    smap[:, T:T + W * N] = T + torch.rand(B, W * N, device="cuda", generator=gen).argsort(1).to(torch.int32)
+
+    def run(lo, hi):
+        k, v, y, yt = (t[lo:hi].clone() for t in (k0, v0, y0, xt))
+        state = None
+        if slots:
+            state = fc.slot_state_alloc(hi - lo, S)
+            state[:(hi - lo) * S] = smap[lo:hi].ravel()
+        kv = fc.KVCache(k, v, T, N, W, 1, trail_tokens=U, slot_map=state)
+        ctx = fc.Context(fc.Caps(max_batch=hi - lo, max_height=28, max_width=28, max_tokens=N,
+                                 max_seq=S, max_d_model=64, max_ffn=ffn, max_qkv=192))
+        fc.fc_layer_forward(ctx, desc, kv, x[lo:hi].clone(), idx[lo:hi].clone(), nrec[lo:hi].clone(), y)
+        fc.fc_layer_forward_trail(ctx, desc, kv, xt[lo:hi].clone(), yt)
+        torch.cuda.synchronize()
+        ctx.close()
+        return k, v, y, yt
+    halves = [torch.cat(p) for p in zip(run(0, B // 2), run(B // 2, B))]
+    for name, a, b in zip("k v y y_trail".split(), run(0, B), halves):
+        assert torch.equal(a, b), name
+    assert not torch.equal(halves[2], y0) and not torch.equal(halves[3], xt)
+
+
 def test_few_row_qkv_operand_is_exact_for_short_gains(fc, ctx):
     """With a power-of-two attention gain the products x g are bf16 numbers, so new K and V rows
     are the rounding of a float32 sum: as far from the 64-bit values as the rounding of those
