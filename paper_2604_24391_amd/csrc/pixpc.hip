@@ -668,37 +668,45 @@ __global__ __launch_bounds__(kPcThreads) void k_pc_rows_inv(int H, int B, PixWs 
         }
     }
     wave_sync();
-    for (int sq = 0; sq < F::S; ++sq) {
-      const int yo = 2 * (g * F::S + sq);
-      if (yo >= H) break;
-      double best[2] = {-INFINITY, -INFINITY};
-      double *row = resp ? resp + ((size_t)b * H + yo) * W : nullptr;
-      for (int x = lane; x < W; x += 64) {
-        const double2 r = buf[sq * W + x];
-        if (row) {
-          row[x] = r.x;
-          row[W + x] = r.y;
-        }
-        if (r.x > best[0]) best[0] = r.x;
-        if (r.y > best[1]) best[1] = r.y;
-      }
+    // 64 / S lanes take the two rows of a sequence
+    constexpr int GL = 64 / F::S, NX = W / GL;
+    const int sq = lane / GL, gl = lane % GL, yo = 2 * (g * F::S + sq);
+    double2 r[NX];
+    double best[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
-        for (int o = 32; o > 0; o >>= 1) best[h] = fmax(best[h], __shfl_xor(best[h], o));
-      // the first element of each row that reaches its maximum (a row of NaN: element 0)
-      const double least[2] = {best[0] - kPcTie * fabs(best[0]), best[1] - kPcTie * fabs(best[1])};
-      int arg[2] = {-1, -1};
-      for (int x0 = 0; x0 < W && (arg[0] < 0 || arg[1] < 0); x0 += 64) {
-        const bool in = x0 + lane < W;
-        const double2 r = buf[sq * W + (in ? x0 + lane : 0)];
-        const unsigned long long m0 = __ballot(in && r.x >= least[0]), m1 = __ballot(in && r.y >= least[1]);
-        if (arg[0] < 0 && m0) arg[0] = x0 + __ffsll(m0) - 1;
-        if (arg[1] < 0 && m1) arg[1] = x0 + __ffsll(m1) - 1;
+    for (int i = 0; i < NX; ++i) {
+      r[i] = buf[sq * W + gl + GL * i];
+      if (r[i].x > best[0]) best[0] = r[i].x;
+      if (r[i].y > best[1]) best[1] = r[i].y;
+    }
+    if (resp && yo < H) {
+      double *row = resp + ((size_t)b * H + yo) * W;
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        row[gl + GL * i] = r[i].x;
+        row[W + gl + GL * i] = r[i].y;
       }
-      if (lane < 2) {
-        ws.rowmax[(size_t)b * H + yo + lane] = lane ? best[1] : best[0];
-        ws.rowarg[(size_t)b * H + yo + lane] = max(lane ? arg[1] : arg[0], 0);
-      }
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int o = GL / 2; o > 0; o >>= 1) best[h] = fmax(best[h], __shfl_xor(best[h], o));
+    // the first element of each row that reaches its maximum (a row of NaN: element 0)
+    int arg[2] = {W, W};
+#pragma unroll
+    for (int i = NX - 1; i >= 0; --i) {
+      if (r[i].x >= best[0] - kPcTie * fabs(best[0])) arg[0] = gl + GL * i;
+      if (r[i].y >= best[1] - kPcTie * fabs(best[1])) arg[1] = gl + GL * i;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int o = GL / 2; o > 0; o >>= 1) arg[h] = min(arg[h], __shfl_xor(arg[h], o));
+      if (arg[h] >= W) arg[h] = 0;
+    }
+    if (gl < 2 && yo < H) {
+      ws.rowmax[(size_t)b * H + yo + gl] = gl ? best[1] : best[0];
+      ws.rowarg[(size_t)b * H + yo + gl] = gl ? arg[1] : arg[0];
     }
     wave_sync();
   }
@@ -726,58 +734,58 @@ __global__ __launch_bounds__(kPcThreads) void k_pc_peak(int H, int W, PixWs ws,
                                                         int zero_shift) {
   __shared__ double bv[kPcWaves];
   __shared__ int by[kPcWaves];
-  __shared__ double part[kPcWaves][4];
+  __shared__ double n[4];
   const int b = blockIdx.x, t = threadIdx.x;
-  const double *rowmax = ws.rowmax + (size_t)b * H;
+  constexpr int NR = (kPcMaxN + kPcThreads - 1) / kPcThreads;
+  double rm[NR];
+  int ra[NR];
   double v = -INFINITY;
-  for (int y = t; y < H; y += blockDim.x) v = fmax(v, rowmax[y]);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = t + kPcThreads * i;
+    rm[i] = y < H ? ws.rowmax[(size_t)b * H + y] : -INFINITY;
+    ra[i] = y < H ? ws.rowarg[(size_t)b * H + y] : 0;
+    v = fmax(v, rm[i]);
+  }
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
   if ((t & 63) == 0) bv[t >> 6] = v;
   __syncthreads();
   for (int i = 0; i < kPcWaves; ++i) v = fmax(v, bv[i]);
-  // the first row that reaches it, and that row's first element (a surface of NaN: element 0)
+  // the first row that reaches it, and that row's first element (a surface of NaN: element 0),
+  // as row * 1024 + column
   const double least = v - kPcTie * fabs(v);
-  int ki = H;
-  for (int y = t; y < H; y += blockDim.x)
-    if (rowmax[y] >= least) ki = min(ki, y);
-  for (int o = 32; o > 0; o >>= 1) ki = min(ki, __shfl_xor(ki, o));
-  if ((t & 63) == 0) by[t >> 6] = ki;
+  int at = 0x7fffffff;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int y = t + kPcThreads * i;
+    if (y < H && rm[i] >= least) at = min(at, y * 1024 + ra[i]);
+  }
+  for (int o = 32; o > 0; o >>= 1) at = min(at, __shfl_xor(at, o));
+  if ((t & 63) == 0) by[t >> 6] = at;
   __syncthreads();
-  for (int i = 0; i < kPcWaves; ++i) ki = min(ki, by[i]);
-  if (ki >= H) ki = 0;
-  const int kj = ws.rowarg[(size_t)b * H + ki];
+  for (int i = 0; i < kPcWaves; ++i) at = min(at, by[i]);
+  static_assert(kPcMaxN <= 1024, "a column in 10 bits");
+  if (at >= H * 1024) at = 0;
+  const int ki = at / 1024, kj = at % 1024;
   const int hw = W / 2 + 1;
   const double2 *G = ws.sa + (size_t)b * H * hw;
   const int yu = (ki - 1 + H) % H, yd = (ki + 1) % H;
-  double n[4] = {0.0, 0.0, 0.0, 0.0};                  // up, down, left, right
-  for (int k = t; k < hw; k += blockDim.x) {
-    const bool real = k == 0 || 2 * k == W;
-    const double wt = real ? 1.0 : 2.0;
-    auto term = [&](int y, int x) {
-      const double2 g = G[strip_at(H, hw, y, k)];
-      double s, c;
-      sincospi(2.0 * (double)((long)k * x % W) / (double)W, &s, &c);
-      return wt * (real ? g.x * c : g.x * c - g.y * s);
-    };
-    n[0] += term(yu, kj);
-    n[1] += term(yd, kj);
-    n[2] += term(ki, (kj - 1 + W) % W);
-    n[3] += term(ki, (kj + 1) % W);
+  // each wave sums one of them: up, down, left, right
+  static_assert(kPcWaves == 4, "a wave per neighbour");
+  const int wv = t >> 6;
+  const int yn = wv == 0 ? yu : wv == 1 ? yd : ki;
+  const int xn = wv < 2 ? kj : wv == 2 ? (kj - 1 + W) % W : (kj + 1) % W;
+  double sum = 0.0;
+  for (int k = t & 63; k < hw; k += 64) {
+    const double2 g = G[strip_at(H, hw, yn, k)];
+    double s, c;
+    sincospi(2.0 * (double)((long)k * xn % W) / (double)W, &s, &c);
+    sum += k == 0 || 2 * k == W ? g.x * c : 2.0 * (g.x * c - g.y * s);
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    for (int o = 32; o > 0; o >>= 1) n[i] += __shfl_xor(n[i], o);
-    if ((t & 63) == 0) part[t >> 6][i] = n[i];
-  }
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if ((t & 63) == 0) n[wv] = sum / ((double)H * (double)W);
   __syncthreads();
   if (t != 0) return;
-  const double hwn = (double)H * (double)W;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    n[i] = part[0][i];
-    for (int w = 1; w < kPcWaves; ++w) n[i] += part[w][i];
-    n[i] /= hwn;
-  }
   const int pi = ki <= H / 2 ? ki : ki - H;
   const int pj = kj <= W / 2 ? kj : kj - W;
   const double di = pi + parabolic(n[0], v, n[1]);
