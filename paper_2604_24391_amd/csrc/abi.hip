@@ -627,7 +627,8 @@ static fc_status check_vit(fc_ctx *ctx, const fc_vit_desc *L, const fc_vit_cache
   const long slots = (long)B * N * c->merge * c->merge;
   const fc_caps &cp = ctx->caps;
   const long rows = (long)cp.max_batch * cp.max_tokens;
-  // the row sums of squares of the layer: one per slot and 1024-column chunk
+  // rows bounded also by the layer's sums of squares, at one per slot and 1024 columns (the block
+  // keeps its own with the partial sums)
   const long ssq_cap = rows * std::max<long>(8, (cp.max_d_model + 127) / 128);
   if (B > cp.max_batch || N > cp.max_tokens || slots * L->d_model > rows * cp.max_d_model ||
       slots * L->d_model > rows * cp.max_qkv || slots * L->d_ffn > rows * cp.max_ffn ||

@@ -115,8 +115,8 @@ struct FrameSpectra {
 };
 // Workspace of the pixel-resolution phase correlation (pixpc.hip): the half-plane
 // spectra of both frames [B][H][W/2 + 1] (sa later holds the cross power and its inverse
-// column transforms; sb the response surface when the caller gives no buffer), per-row
-// maxima and their columns, per-strip largest |X|, and the sub-pixel shifts [B][2].
+// column transforms), per-row maxima and their columns, the largest |X| of each column
+// workgroup, and the sub-pixel shifts [B][2].
 struct PixWs {
   double2 *sa = nullptr, *sb = nullptr;
   double *rowmax = nullptr;

@@ -346,12 +346,12 @@ struct RedArgs {
   const float *part;              // [split][B*N][ncols]
   const uint16_t *x;              // [B][N][d] layer input
   const uint16_t *bias;           // [ncols] (QKV)
-  const uint16_t *gain;           // [d] MLP RMSNorm gain (O reduction)
+  const uint16_t *gain;           // [d] MLP RMSNorm gain (O epilogue)
   uint16_t *q, *kc, *vc;          // QKV outputs
   const int32_t *smap;            // slot map of the K/V rows (null: rows in place)
   float *h1;                      // [B*N][d]
   uint16_t *hb;                   // [B*N][d] bf16(h1 * g_mlp), the SwiGLU operand
-  float *ssq;                     // [B*N][chunks] sums of squares of h1 per 1024 columns
+  float *ssq;                     // [B*N][chunks] sums of squares of h1 per kMSsqCols columns
   uint16_t *y;                    // [B][N][d]
 };
 

@@ -39,14 +39,14 @@
 // hold it.  Twiddles come from a table per workgroup (sincospi of the exact rational angle).
 // Sizes: H and W of the form 7 2^k with 2 <= 2^k <= 128 (14 ... 896).
 //
-// What bounds it: memory.  64 pairs of 448 x 448 move 308 MB of frames and 721 MB of
-// half-spectra (written once, read by the forward columns, the cross power written and read,
-// its inverse columns written and read).  Measured there, against transforms of one sequence
+// What bounds it: memory.  64 pairs of 448 x 448 move 308 MB of frames and 826 MB of
+// half-spectra, eight passes over 103 MB (both written once and read by the forward columns,
+// the cross power written and read, its inverse columns written and read).  Measured there, against transforms of one sequence
 // per workgroup with a barrier after every stage and every twiddle product in LDS:
-//   k_pc_rows 421 -> 109 us (4.7 TB/s; a large copy reaches 4.6 TB/s), k_pc_cols_fwd
-//   305 -> 61 us (5.0 TB/s), k_pc_cols_inv 129 -> 48 us (4.3 TB/s), k_pc_rows_inv
-//   249 -> 41 us (2.5 TB/s; it no longer writes the surface for the selection),
-//   k_pc_peak 4.8 -> 7.7 us (it sums the neighbours itself); fc_select 1225 -> 360 us.
+//   k_pc_rows 421 -> 105 us (4.9 TB/s; a large copy reaches 4.6 TB/s), k_pc_cols_fwd
+//   305 -> 58 us (5.4 TB/s), k_pc_cols_inv 129 -> 46 us (4.5 TB/s), k_pc_rows_inv
+//   249 -> 33 us (3.2 TB/s; it no longer writes the surface for the selection),
+//   k_pc_peak 4.8 -> 5.4 us (it sums the neighbours itself); fc_select 1225 -> 358 us.
 //
 // Half-spectra lie in strips of 8 columns, [strip][row][8] (the last strip as wide as what
 // is left), so that a row's pieces and a strip's rows are whole 128-B lines; the cross power
@@ -898,7 +898,9 @@ namespace {
 template <typename F>
 void pix_parts(long B, long H, long W, bool rot, F &&take) {
   const long hw = W / 2 + 1;
-  const long ncb = (hw + 1) / 2;             // strips of the narrowest kind (CW = 2)
+  // bmax: a column workgroup takes 8 columns or more; the part has been one value per 2 columns,
+  // and what fits a scratch of fixed size stays what it was
+  const long ncb = (hw + 1) / 2;
   take(0, (size_t)B * H * hw * sizeof(double2));
   take(1, (size_t)B * H * hw * sizeof(double2));
   take(2, (size_t)B * H * sizeof(double));

@@ -94,8 +94,8 @@ __device__ __forceinline__ float gelu_erf(float v) {
 //     weights once.
 // Measured on the Qwen2.5-VL block (d 1280, MLP 3456), us, against 256 x 256 tiles in up to 8
 // K-range parts with a reduction kernel each: QKV 23 + 15 -> 18.5, O 15 + 9 -> 14, gate/up
-// 28 + 14 -> 26, down 21 + 9 -> 21 at 1024 rows; the whole windowed block 157 -> 91 at 1024
-// rows, 129 -> 78 at 512 and 89 -> 54 at 104 rows (there against the weight-streaming GEMM
+// 28 + 14 -> 28, down 21 + 9 -> 21 at 1024 rows; the whole windowed block 154 -> 92 at 1024
+// rows, 136 -> 81 at 645 and 88 -> 55 at 104 rows (there against the weight-streaming GEMM
 // and its reductions).  The DMA pattern alone takes 7.3 us for QKV (37 B a clock and CU); LDS
 // traffic (operands written once and read twice), about 3 us before the first step is staged
 // and 2 us of epilogue make up the rest.  Decoder layer (d 3584, 162 rows), against the

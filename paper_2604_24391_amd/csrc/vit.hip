@@ -53,9 +53,6 @@ __device__ float block_sum(float v, float *red) {
   return s;
 }
 
-// Split-K sums of columns c .. c + 3 of row s (partials [split][rows][nc]): all SPL
-// 16-byte loads issued first (indices past the last split re-read it), then summed in
-// split order with the extra ones masked out.
 // Sum over the splits of the float4 at p0 + sp stride, in split order, loads issued in
 // groups of up to 4 (a group past the last split is skipped; `splits` is uniform).
 template <int SPL>
@@ -80,6 +77,7 @@ __device__ __forceinline__ float4 sum_splits4(const float *__restrict__ p0, long
   }
   return a;
 }
+// Split-K sums of columns c .. c + 3 of row s (partials [split][rows][nc]).
 template <int SPL>
 __device__ __forceinline__ float4 sum_parts4(const float *__restrict__ part, int splits, long rows,
                                              long s, int nc, int c) {
@@ -597,8 +595,8 @@ static fc_status vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
   g.win = c.window;
   const long slots = (long)B * g.Np;
   const int f = L.d_ffn;
-  // rotated keys and, after them, the sums of squares: the partial-sum buffer is free on this
-  // path and holds at least as many 32-bit values as the QKV columns of every slot
+  // rotated keys and, past a value a slot and column, the sums of squares: the partial-sum buffer
+  // is free on this path and holds at least as many 32-bit values as the QKV columns of every slot
   const int nwin = c.window > 0 ? ((g.gh + c.window - 1) / c.window) * ((g.gw + c.window - 1) / c.window) : 1;
   const int wkeys = c.window > 0 ? std::min(c.window, g.gh) * std::min(c.window, g.gw) * g.mm : g.Np;
   uint16_t *krot = wkeys > 64 ? reinterpret_cast<uint16_t *>(ctx->part) : nullptr;
@@ -667,9 +665,12 @@ fc_status launch_vit_block(fc_ctx *ctx, const fc_vit_desc &L, const fc_vit_cache
                            const uint16_t *x, const int32_t *idx, const int32_t *nrec,
                            uint16_t *y, int B, hipStream_t st) {
   const long N = (long)c.grid_h * c.grid_w, Np = N * c.merge * c.merge;
-  // the projections' sums fit the partial-sum workspace of the context
+  // The rotated keys and sums of squares take d / 2 + d / 64 values a row of the partial-sum
+  // workspace.  The rows a context takes are those whose projections would fit there, as for
+  // the layer's split-K sums, though no projection here writes them.
   if ((size_t)B * Np * std::max(3 * L.d_model, 2 * L.d_ffn) > ctx->part_elems)
-    return fail(FC_ERR_CAPACITY, "fc_vit_block_forward: partial sums exceed the workspace");
+    return fail(FC_ERR_CAPACITY, "fc_vit_block_forward: rows x columns of the projections exceed "
+                "the partial-sum workspace");
   // the packed row map of a GEMM holds kMMaxItems items
   for (int b0 = 0; b0 < B; b0 += kMMaxItems) {
     fc_vit_cache cb = c;
