@@ -373,6 +373,8 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm &a, unsigned char *l
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float gv = v4[i] * inv + bb0[i], uv = u4[i] * inv + bb1[i];
+          // expf and a division: __expf (some 80 ulp off at -80) and v_rcp_f32 would save 2 of a
+          // block's 81 us
           x0[i] = gv / (1.f + expf(-gv)) * uv;
         }
         st_bf4(a.act + (long)rslot[r] * (a.cols / 2) + p, x0[0], x0[1], x0[2], x0[3]);
