@@ -148,7 +148,8 @@ constexpr int row_streams(int K) { return K < 5120 ? 1 : K < 9216 ? 2 : 3; }
 // Which of the two a call takes.  Every item has at least one recomputed row as a rule, so the
 // number of items decides alone where it reaches row_streams (an item without rows then costs
 // time, not its result).  Where the slots could hold that many streams but the items need not,
-// the rows decide, on the device (nrec null: every slot is a row).
+// the rows decide, on the device, which costs a launch some 0.7 us, and an empty reduction where
+// the row tiles are taken (nrec null: every slot is a row).
 enum Route { kStream, kRowTiles, kOnDevice };
 inline Route row_route(int K, int B, int N, const int32_t *nrec) {
   const int need = row_streams(K);

@@ -353,6 +353,39 @@ def test_merger_kernel_follows_the_rows(fc, ctx, n):
     assert torch.equal(run(520, 1), run(256, 1) if n <= 256 else run(520, 2))
 
 
+def test_captured_merger_follows_the_rows(fc, ctx):
+    """One captured merger call replayed while the recomputed rows go from 100 to 400 and back:
+    the kernel is chosen at each replay, whose bytes are those of an eager call."""
+    sh = fcdata.MergerShape(d=640, m=3, d_out=80)
+    desc = merger_desc(fc, fcdata.merger_weights(383, sh), sh)
+    gen = torch.Generator("cuda").manual_seed(385)
+    y = torch.randn(1, 520 * 9, sh.d, device="cuda", generator=gen).to(torch.bfloat16)
+    idx = torch.arange(520, dtype=torch.int32, device="cuda")[None].contiguous()
+    nrec = torch.tensor([100], dtype=torch.int32, device="cuda")
+    x = torch.zeros(1, 520, sh.d_out, dtype=torch.bfloat16, device="cuda")
+
+    def call():
+        fc.fc_vit_merger_forward(ctx, desc, y, idx, nrec, x)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for n in (100, 400, 100, 256, 257):
+        nrec.fill_(n)
+        x.zero_()
+        call()
+        want = x.clone()
+        x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, want) and x[0, n - 1].any() and not x[0, n:].any()
+
+
 def test_merger_qwen_shape(fc, ctx):
     """The Qwen2.5-VL merger (1280 x 4 = 5120 -> 5120 -> 3584) on a 448 x 448 frame's 256
     tokens, half of them recomputed."""
